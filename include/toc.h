@@ -228,7 +228,8 @@ toc_status toc_dev_layout_get(const toc_dev *dev, toc_layout *layout);
  * Device operations.  Workspace: toc_workspace_size gives the bytes an op needs
  * to run in one pass over all batches; an op given less (but at least its
  * per-batch minimum, returned in *min_bytes when not NULL) runs in several
- * passes; less than the minimum is TOC_ESIZE.  A size of 0 means ws may be NULL.
+ * passes or with other kernels (the same result within rounding); less than the
+ * minimum is TOC_ESIZE.  A size of 0 means ws may be NULL.
  * The workspace is scratch: its contents on entry do not matter.
  * op: TOC_OP_RIGHT, TOC_OP_LEFT, TOC_OP_DECODE.
  * ------------------------------------------------------------------------- */
@@ -263,8 +264,8 @@ toc_status toc_left_mul(const toc_dev *dev, const float *G, int32_t k, int64_t l
 
 /* Left multiplication without any allocation, for callers that cannot allocate
  * device memory (work captured into a HIP graph, tight serving loops, harnesses
- * that forbid hipMalloc).  The same product as toc_left_mul, bit for bit, with no
- * workspace argument: the workspace is a static device buffer of
+ * that forbid hipMalloc).  The same product as toc_left_mul given the workspace that
+ * toc_workspace_size asks for, bit for bit, with no workspace argument: the workspace is a static device buffer of
  * TOC_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on until
  * the process ends (its address is looked up on the first call on each device).
  * When the full grid's per-worker slots do not fit in it, fewer persistent

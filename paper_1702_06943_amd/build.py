@@ -20,7 +20,7 @@ ARCH = "gfx950"
 NO_PACKED_FP32 = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 HOST_SOURCES = ("toc_host.cpp", "toc_phys.cpp")
 HIP_SOURCES = ("toc_device.hip", "toc_cprime.hip", "toc_mgd.hip", "toc_encode.hip", "toc_mlp.hip",
-               "toc_ingest.hip")
+               "toc_ingest.hip", "toc_mfma.hip")
 
 
 def _run(cmd, verbose):

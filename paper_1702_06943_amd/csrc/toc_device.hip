@@ -3215,6 +3215,7 @@ toc_status toc_workspace_size(const toc_dev *d, int32_t op, int32_t k, size_t *b
       minimum = (size_t)(p.rows_max * p.row_floats * 4);
       need = std::max(minimum, (size_t)(p.rows_total * p.row_floats * 4));
     }
+    if (toc::mfma_suits(d, k, op == TOC_OP_RIGHT)) need = std::max(need, toc::mfma_workspace(d));
   }
   *bytes = need;
   if (min_bytes) *min_bytes = minimum;
@@ -3261,6 +3262,8 @@ toc_status toc_right_mul(const toc_dev *d, const float *W, int32_t k, int64_t ld
     if (plan.ws_floats > 0 && (!ws || ws_bytes < (size_t)plan.ws_floats * 4))
       return fail(TOC_ESIZE, "workspace of %zu bytes below the %lld needed", ws_bytes,
                   (long long)plan.ws_floats * 4);
+    if (toc::mfma_fits(d, k, true, ldw, ws, ws_bytes))
+      return toc::right_mfma(d, W, k, ldw, R, ldr, ws, ws_bytes, stream);
     const int m = d->info.n_cols;
     if (plan.compact) {
       if ((st = allow_lds(right_compact_kernel, plan.lds))) return st;
@@ -3284,6 +3287,8 @@ toc_status toc_right_mul(const toc_dev *d, const float *W, int32_t k, int64_t ld
   }
   int64_t cap_rows = 0;
   if ((st = ws_capacity(plan, ws, ws_bytes, cap_rows))) return st;
+  if (toc::mfma_fits(d, k, true, ldw, ws, ws_bytes))
+    return toc::right_mfma(d, W, k, ldw, R, ldr, ws, ws_bytes, stream);
   for (int64_t k0 = 0; k0 < k; k0 += kKTile) {
     const int kt = (int)std::min<int64_t>(kKTile, k - k0);
     const int kpl = (kt + kWave - 1) / kWave;
@@ -3365,6 +3370,8 @@ toc_status left_mul_impl(const toc_dev *d, const float *G, int32_t k, int64_t ld
     if (plan.ws_floats > 0 && (!ws || ws_bytes < (size_t)plan.ws_floats * 4))
       return fail(TOC_ESIZE, "workspace of %zu bytes below the %lld needed", ws_bytes,
                   (long long)plan.ws_floats * 4);
+    if (toc::mfma_fits(d, k, false, ldo, ws, ws_bytes))
+      return toc::left_mfma(d, G, k, ldg, out, ldo, accumulate, ws, ws_bytes, stream);
     const uint8_t *bb = (const uint8_t *)d->buf;
     const uint32_t *occ_off = (const uint32_t *)(bb + d->layout.occ_off);
     const uint32_t *tlist = (const uint32_t *)(bb + d->layout.tlist);
@@ -3393,6 +3400,8 @@ toc_status left_mul_impl(const toc_dev *d, const float *G, int32_t k, int64_t ld
   }
   int64_t cap_rows = 0;
   if ((st = ws_capacity(plan, ws, ws_bytes, cap_rows))) return st;
+  if (toc::mfma_fits(d, k, false, ldo, ws, ws_bytes))
+    return toc::left_mfma(d, G, k, ldg, out, ldo, accumulate, ws, ws_bytes, stream);
   for (int64_t k0 = 0; k0 < k; k0 += kKTile) {
     const int kt = (int)std::min<int64_t>(kKTile, k - k0);
     const int kpl = (kt + kWave - 1) / kWave;

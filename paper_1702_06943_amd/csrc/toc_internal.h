@@ -94,4 +94,17 @@ struct BatchCounts {
 toc_status plan_layout(const BatchCounts *bc, int64_t n_batches, int32_t n_cols, uint32_t flags,
                        toc_dev *dev);
 
+// Products with k >= 2 on the matrix cores (toc_mfma.hip).  mfma_suits: whether they are
+// the faster ones for an image and an operand of k columns; mfma_workspace: the
+// workspace bytes they ask for; mfma_fits: whether a call (row stride ld of W or out,
+// workspace) can take them.  The arguments of the other two are those of toc_left_mul /
+// toc_right_mul, already checked (stream: a hipStream_t).
+bool mfma_suits(const toc_dev *d, int32_t k, bool right);
+size_t mfma_workspace(const toc_dev *d);
+bool mfma_fits(const toc_dev *d, int32_t k, bool right, int64_t ld, const void *ws, size_t ws_bytes);
+toc_status left_mfma(const toc_dev *d, const float *G, int32_t k, int64_t ldg, float *out,
+                     int64_t ldo, int32_t accumulate, void *ws, size_t ws_bytes, void *stream);
+toc_status right_mfma(const toc_dev *d, const float *W, int32_t k, int64_t ldw, float *R,
+                      int64_t ldr, void *ws, size_t ws_bytes, void *stream);
+
 }  // namespace toc

@@ -1,0 +1,1065 @@
+// Wide-k products on the matrix cores (gfx950): R = A.W and out = (G^T A)^T for
+// batches of up to 256 tuples whose used columns are filled densely enough.
+//
+// The matrix cores run bf16 products with binary32 accumulation at 16 times the
+// vector units' rate, so a batch is expanded on the chip, 32 of its used columns at
+// a time, into LDS tiles of bf16, and never in memory.  Operands keep their 24-bit
+// significands: a binary32 value is split exactly into three bf16 parts,
+// x = x1 + x2 + x3 with |x2| <= 2^-7 |x|, |x3| <= 2^-15 |x|, and a product x.y is the
+// sum of the parts' products x1y1 + x1y2 + x2y1 + x1y3 + x2y2 + x3y1; what is left out
+// is below 2^-22 |x||y| and of both signs (the dense operand's parts are rounded to
+// nearest).  A chunk whose values all have x2 = x3 = 0 (integers below 256, 1.0,
+// sixteenths) takes the three products of x1 alone, an exact shortcut decided from
+// the chunk's own values.
+//
+// Sums are formed in blocks, the small products first: the right product adds the 32
+// terms of a chunk to an output at once, the left product keeps the small products of
+// all tuples apart from the large ones x1y1 until the end.
+//
+// Parts of values near the ends of the exponent range would be lost, and an
+// infinity or NaN of the dense operand must not reach tuples without that column
+// (0 times infinity): a tile whose operands hold a non-finite value, or a nonzero
+// one outside the ranges below, is computed term by term in binary32 instead.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "toc_internal.h"
+
+using toc::fail;
+
+namespace {
+
+constexpr int kWave = 64;
+constexpr int kXcd = 8;
+constexpr int kThreads = 512;                 // 8 waves, 2 per SIMD: 256 registers each
+constexpr int kChunk = 32;                    // used columns per LDS tile
+constexpr uint32_t kRowMask = 0x3fffffffu;    // row of a leaf occurrence word
+constexpr uint32_t kLeftRow = (kChunk + 4) * 16;   // bytes of a slot row of the left product's tile
+constexpr uint32_t kSpare = kWave * 4;         // bytes after a plane: a word per lane without an entry
+
+// |x| of the compressed values in [2^-32, 2^50], of the dense operand in
+// [2^-70, 2^60], zeros apart: every part and product is then a normal number or
+// below 2^-24 of its sum's terms, and no sum overflows.
+constexpr uint32_t kValLo = (127 - 32) << 23, kValHi = (127 + 50) << 23;
+constexpr uint32_t kDenseLo = (127 - 70) << 23, kDenseHi = (127 + 60) << 23;
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// stores of both kinds go to one LDS tile
+typedef uint16_t __attribute__((may_alias)) tile_u16;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef u32x4 __attribute__((may_alias)) tile_u32x4;
+typedef u32x2 __attribute__((may_alias)) tile_u32x2;
+typedef __attribute__((address_space(3))) tile_u16 lds_u16;
+
+__device__ inline uint32_t lds_address(const char *p) {
+  return (uint32_t)(size_t)(__attribute__((address_space(3))) const char *)p;
+}
+
+__device__ inline f32x4 mfma(u32x4 a, u32x4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Three bf16 parts of 8 values, rounded to nearest.
+__device__ inline void split8(const float (&x)[8], u32x4 (&p)[3]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float a = x[2 * i], c = x[2 * i + 1];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      const f32x2 v = {a, c};
+      const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+      p[s][i] = w;
+      a -= __uint_as_float(w << 16);
+      c -= __uint_as_float(w & 0xffff0000u);
+    }
+  }
+}
+
+// Running bounds of |x| over nonzero x, on the bits.
+struct Range {
+  uint32_t hi = 0, lo = 0xffffffffu;
+  __device__ void add(uint32_t bits) {
+    const uint32_t a = bits & 0x7fffffffu;
+    hi = max(hi, a);
+    lo = min(lo, a - 1u);           // a zero wraps to the top
+  }
+  __device__ bool outside(uint32_t low, uint32_t high) const { return hi > high || lo < low - 1u; }
+};
+
+__device__ inline int64_t uniform64(int64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+struct MfmaImg {
+  const toc_batch *batches;
+  const toc_key *key;
+  const toc_link *link;
+  const uint32_t *span, *dcodes, *centry, *cval, *occ_off, *tlist, *cols, *tchild;
+  // expanded tree codes (tree_expand_kernel) of batches b0 ..: pairs per column, and
+  // the pairs (tuple, value bits), x_stride of them to a batch, column j's from
+  // j n_rows - (leaf occurrences of the columns before it)
+  const uint32_t *xn;
+  const uint2 *xpair;
+  int64_t b0, n_stride, x_stride;
+};
+
+// One batch's column entries and tree, in wave-uniform registers.
+struct Batch {
+  const uint32_t *ce, *cv;       // entries and their values
+  __amdgpu_buffer_rsrc_t ce_res, cv_res, x_res;   // range-checked; x: expanded pairs
+  const uint32_t *xn;            // expanded pairs per column
+  const toc_key *key;
+  const uint32_t *occ, *tf;      // per column: leaf occurrences before it, tree-list start
+  const uint32_t *order;         // columns, most entries first, those without last
+  const uint32_t *to, *tch, *tl; // per tree row: occurrences, children; tree codes by column
+  uint32_t n_used, ni, n1, n_tree, tbase;
+  int n_rows;
+  int64_t row_base;
+};
+
+__device__ inline Batch load_batch(const MfmaImg &im, int64_t b, int m) {
+  const toc_batch *p = im.batches + b;
+  Batch t;
+  const int64_t code_base = uniform64(p->code_base), d_base = uniform64(p->d_base),
+                tree_base = uniform64(p->tree_base);
+  t.row_base = uniform64(p->row_base);
+  t.n_rows = __builtin_amdgcn_readfirstlane(p->n_rows);
+  t.ni = (uint32_t)__builtin_amdgcn_readfirstlane(p->n_int1);
+  t.n1 = (uint32_t)__builtin_amdgcn_readfirstlane(p->n_lvl1);
+  t.n_used = (uint32_t)__builtin_amdgcn_readfirstlane(p->n_ucols);
+  t.ce = im.centry + d_base + tree_base;
+  t.cv = im.cval + d_base + tree_base;
+  const uint32_t *c = im.cols + b * 4 * (int64_t)(m + 1);
+  t.n_tree = t.ni + (uint32_t)__builtin_amdgcn_readfirstlane(p->n_codes) - t.n1;
+  const int n_entries = __builtin_amdgcn_readfirstlane(p->n_d) + (int)t.n_tree;
+  t.ce_res = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(t.ce), (short)0, n_entries * 4,
+                                               0x00020000);
+  t.cv_res = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(t.cv), (short)0, n_entries * 4,
+                                               0x00020000);
+  t.occ = c + (m + 1);
+  t.tf = c + 2 * (int64_t)(m + 1);
+  t.order = c + 3 * (int64_t)(m + 1);
+  t.tbase = (uint32_t)__builtin_amdgcn_readfirstlane((int)t.occ[m]);
+  t.to = im.occ_off + code_base + 2 * b + (t.n1 - t.ni) + 1;
+  t.tch = im.tchild + tree_base + b;
+  t.tl = im.tlist + tree_base;
+  t.x_res = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint2 *>(im.xpair + (b - im.b0) * im.x_stride), (short)0, (int)(im.x_stride * 8),
+      0x00020000);
+  t.xn = im.xn + (b - im.b0) * im.n_stride;
+  t.key = im.key + code_base;
+  return t;
+}
+
+// Calls put(row) for every tuple whose sequence passes through tree rows a .. e-1 (codes
+// of one level) or their descendants.  The descendants one level down are
+// consecutive codes and so are their occurrences, so each level is one stretch of
+// entries.
+template <typename F>
+__device__ inline void tree_rows(const Batch &t, uint32_t a, uint32_t e, F put) {
+  uint32_t o0 = t.to[a], o1 = t.to[e], c0 = t.tch[a], c1 = t.tch[e];
+  for (;;) {
+    // the next level's places and this level's first tuples in flight together
+    const uint32_t x0 = o0 < o1 ? t.ce[o0] : 0u, x1 = o0 + 1 < o1 ? t.ce[o0 + 1] : 0u;
+    const uint32_t p0 = o0, p1 = o1;
+    const bool more = c0 < c1;
+    if (more) {
+      a = c0 - t.n1 + t.ni;
+      e = c1 - t.n1 + t.ni;
+      o0 = t.to[a], o1 = t.to[e], c0 = t.tch[a], c1 = t.tch[e];
+    }
+    if (p0 < p1) put(x0 & kRowMask);
+    if (p0 + 1 < p1) put(x1 & kRowMask);
+    for (uint32_t o = p0 + 2; o < p1; ++o) put(t.ce[o] & kRowMask);
+    if (!more) break;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The tree codes of the batches, expanded column by column: for every column the
+// tuples whose sequences pass through one of its tree codes, with the code's value.  They
+// are a small part of a batch's pairs (2 % of an image-like batch, 14 % of a dense
+// quantised one), but each is found through up to two dependent loads per level of
+// its subtree: done here once per call, a thread per code, instead of inside the
+// products' pipelines once per tile of columns (there it took half of the dense
+// quantised batches' time).  A column has room for the tuples that hold none of its
+// leaves, so its place needs no scan; a code takes its pairs' places in the column
+// level by level, the lanes of one column with one atomic addition (an addition per
+// code took 590 us for 100 dense quantised batches, counting the subtrees first 112 us,
+// this 97 us).  The order of a column's pairs varies from run to run and does not
+// matter: each fills a tile cell of its own.
+// xn: pairs of each column so far, zero on entry.
+// ---------------------------------------------------------------------------
+constexpr int kExpandThreads = 256;
+
+__global__ __launch_bounds__(256) void tree_zero_kernel(u32x4 *__restrict__ xn, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) xn[i] = u32x4{0, 0, 0, 0};
+}
+
+__global__ __launch_bounds__(kExpandThreads) void tree_expand_kernel(MfmaImg im, int m, int blocks,
+                                                                     uint32_t *__restrict__ xn,
+                                                                     uint2 *__restrict__ xpair) {
+  const int64_t bi = blockIdx.x / blocks;
+  const Batch t = load_batch(im, im.b0 + bi, m);
+  const int lane = threadIdx.x % kWave;
+  const uint32_t n_tree = t.n_tree;
+  for (uint32_t s0 = (uint32_t)(blockIdx.x % blocks) * kExpandThreads; s0 < n_tree;
+       s0 += (uint32_t)blocks * kExpandThreads) {
+    const uint32_t s = s0 + threadIdx.x;
+    const bool there = s < n_tree;
+    uint32_t j = 0xffffffffu, v = 0, o0 = 0, o1 = 0, c0 = 0, c1 = 0;
+    if (there) {
+      const uint32_t y = t.tl[s], a = y < t.ni ? y : y - t.n1 + t.ni;
+      v = t.cv[t.tbase + s];
+      j = t.key[y].col;
+      o0 = t.to[a], o1 = t.to[a + 1], c0 = t.tch[a], c1 = t.tch[a + 1];
+    }
+    uint32_t *next = xn + bi * im.n_stride + j;
+    uint2 *w = xpair + bi * im.x_stride + (there ? (int64_t)j * t.n_rows - t.occ[j] : 0);
+    // lanes of one column are neighbours: whether the lane o below is of the same one,
+    // and the column's last lane
+    bool same[6];
+#pragma unroll
+    for (int o = 0; o < 6; ++o)
+      same[o] = (uint32_t)__shfl_up((int)j, 1 << o, kWave) == j && lane >= 1 << o;
+    const uint32_t above = (uint32_t)__shfl_down((int)j, 1, kWave);
+    const bool last = lane == kWave - 1 || above != j;
+    const int last_lane = lane + __ffsll((unsigned long long)(__ballot(last) >> lane)) - 1;
+    while (__any(o0 < o1 || c0 < c1)) {
+      // one level of every lane's subtree: its places in the column, its first tuples
+      // and the next level's places are in flight together
+      const uint32_t p0 = o0, n = o1 - o0;
+      uint32_t x[4];
+#pragma unroll
+      for (uint32_t i = 0; i < 4; ++i) x[i] = i < n ? t.ce[p0 + i] : 0u;
+      const bool more = c0 < c1;
+      const uint32_t a = c0 - t.n1 + t.ni, e = c1 - t.n1 + t.ni;
+      o0 = o1 = c0 = c1 = 0;
+      if (more) o0 = t.to[a], o1 = t.to[e], c0 = t.tch[a], c1 = t.tch[e];
+      uint32_t sum = n;
+#pragma unroll
+      for (int o = 0; o < 6; ++o) {
+        const uint32_t u = (uint32_t)__shfl_up((int)sum, 1 << o, kWave);
+        if (same[o]) sum += u;
+      }
+      uint32_t first = 0;
+      if (last && sum) first = atomicAdd(next, sum);
+      first = (uint32_t)__shfl((int)first, last_lane, kWave) + (sum - n);
+#pragma unroll
+      for (uint32_t i = 0; i < 4; ++i)
+        if (i < n) w[first + i] = make_uint2(x[i] & kRowMask, v);
+      for (uint32_t i = 4; i < n; ++i) w[first + i] = make_uint2(t.ce[p0 + i] & kRowMask, v);
+    }
+  }
+}
+
+// Where the used columns of the chunks in flight find their entries: written by the
+// first wave, from the column index loaded one and two chunks before.
+constexpr int kRing = 6;
+struct Ring {
+  u32x4 at[kRing][kChunk];        // leaf occurrences: first and number; pairs: first and number
+  uint32_t off[kRing][kChunk];    // byte offset of the column's row of W or out, or kNone
+  uint32_t steps[kRing][kChunk];  // of 4 columns: most 16-entry steps of leaves, of pairs << 16
+};
+constexpr uint32_t kNone = 0x80000000u;
+
+struct RingLoad {
+  uint32_t jn, jp, l0, l1, x;
+  __device__ void places(const Batch &t) {
+    l0 = l1 = x = 0;
+    if (jp != 0xffffffffu) {
+      l0 = t.occ[jp];
+      l1 = t.occ[jp + 1];
+      x = t.xn[jp];
+    }
+  }
+  __device__ void publish(const Batch &t, Ring &ring, int slot, uint32_t i, uint32_t row_bytes) {
+    ring.off[slot][i] = jp == 0xffffffffu ? kNone : jp * row_bytes;
+    ring.at[slot][i] = u32x4{l0, l1 - l0, jp * (uint32_t)t.n_rows - l0, x};
+    uint32_t a = (l1 - l0 + 15u) / 16u, b = (x + 15u) / 16u;
+    a = max(a, (uint32_t)__shfl_xor((int)a, 1, kWave));
+    b = max(b, (uint32_t)__shfl_xor((int)b, 1, kWave));
+    a = max(a, (uint32_t)__shfl_xor((int)a, 2, kWave));
+    b = max(b, (uint32_t)__shfl_xor((int)b, 2, kWave));
+    ring.steps[slot][i] = a | b << 16;
+  }
+  __device__ static uint32_t column(const Batch &t, uint32_t at) {
+    return at < t.n_used ? t.order[at] : 0xffffffffu;
+  }
+  // the first three chunks' places, by the first wave (before a barrier); the loads
+  // of the fourth's and of the fifth's columns on their way
+  __device__ void start(const Batch &t, Ring &ring, uint32_t row_bytes) {
+    if (threadIdx.x >= kWave) return;
+    const uint32_t i = threadIdx.x;
+    jp = column(t, i);
+    const uint32_t j2 = column(t, 2 * kChunk + i % kChunk);
+    const uint32_t j3 = column(t, 3 * kChunk + i % kChunk);
+    jn = column(t, 4 * kChunk + i % kChunk);
+    places(t);
+    publish(t, ring, (int)(i / kChunk), i % kChunk, row_bytes);
+    jp = j2;
+    places(t);
+    publish(t, ring, 2, i % kChunk, row_bytes);
+    jp = j3;
+    places(t);
+  }
+  // one step per chunk: the places of chunk c + 4 to the ring, c + 5's from the
+  // index, c + 6's columns from the order
+  __device__ void step(const Batch &t, Ring &ring, int c, uint32_t row_bytes) {
+    if (threadIdx.x >= kChunk) return;
+    const uint32_t i = threadIdx.x;
+    publish(t, ring, (c + 4) % kRing, i, row_bytes);
+    jp = jn;
+    places(t);
+    jn = column(t, (uint32_t)(c + 6) * kChunk + i);
+  }
+};
+
+// The entries of a chunk's columns on their way from memory to the LDS tile: a 16-lane
+// group takes column kk of every chunk, its leaf occurrences from the image and its
+// expanded pairs from the workspace.  load() issues the loads, a chunk's time
+// before store() uses them: STEPS x 16 leaf occurrences and kXSteps x 16 pairs; a
+// column with more has the rest loaded by store().
+//
+// store() is the serial part of a workgroup's time (one wave per SIMD runs it while
+// the other multiplies), so its steps are short and free of branches: address, the
+// value's high half to plane 0 (lanes without an entry write to a spare word), and the
+// low halves gathered to see whether planes 1 and 2 are needed at all; they are
+// written by a second pass over the same registers.
+template <int STEPS>
+struct Feed {
+  static constexpr int kXSteps = 2;
+  u32x4 at;                              // of the ring; [0] and [2] as byte offsets
+  uint32_t steps, xsteps;
+  uint32_t w[STEPS], v[STEPS], xw[kXSteps], xv[kXSteps];
+
+  __device__ void load(const Batch &t, const Ring &ring, int c, uint32_t kk, uint32_t sub) {
+    at = ring.at[c % kRing][kk];
+    const uint32_t n =
+        (uint32_t)__builtin_amdgcn_readfirstlane((int)ring.steps[c % kRing][kk & ~3u]);
+    at[0] = (at[0] + 2u * sub) * 4u;
+    at[2] = (at[2] + sub) * 8u;
+    steps = n & 0xffffu, xsteps = n >> 16;
+#pragma unroll
+    for (int i = 0; i < STEPS; i += 2) {
+      if ((uint32_t)i < steps) {
+        // two entries a lane; past the column's end: some other entry or none, not stored
+        const auto y = __builtin_amdgcn_raw_buffer_load_b64(t.ce_res, at[0], 64 * i, 0);
+        const auto z = __builtin_amdgcn_raw_buffer_load_b64(t.cv_res, at[0], 64 * i, 0);
+        w[i] = y[0], w[i + 1] = y[1];
+        v[i] = z[0], v[i + 1] = z[1];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kXSteps; ++i) {
+      if ((uint32_t)i < xsteps) {
+        const auto y = __builtin_amdgcn_raw_buffer_load_b64(t.x_res, at[2], 128 * i, 0);
+        xw[i] = y[0];
+        xv[i] = y[1];
+      }
+    }
+  }
+
+  // place(word): the LDS address of the entry's cell in plane 0; spare: an address for
+  // lanes without an entry.  Returns whether the wave wrote planes 1 and 2.
+  template <typename P>
+  __device__ bool store(const Batch &t, uint32_t sub, uint32_t plane, uint32_t spare, Range &range,
+                        P place) const {
+    uint32_t low = 0;
+    auto high = [&](uint32_t word, uint32_t bits, uint32_t i, uint32_t n) {
+      const uint32_t to = i < n ? place(word) : spare;
+      *(lds_u16 *)(size_t)to = (uint16_t)(bits >> 16);
+      low |= bits << 16;
+      range.add(bits);
+    };
+#pragma unroll
+    for (int i = 0; i < STEPS; i += 2) {
+      if ((uint32_t)i < steps) {
+        high(w[i], v[i], 16u * i + 2u * sub, at[1]);
+        high(w[i + 1], v[i + 1], 16u * i + 2u * sub + 1u, at[1]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kXSteps; ++i)
+      if ((uint32_t)i < xsteps)
+        high(xw[i], 16u * i + sub < at[3] ? xv[i] : 0u, 16u * i + sub, at[3]);
+    bool both = __any(low != 0);
+    auto rest = [&](uint32_t word, uint32_t bits, uint32_t i, uint32_t n) {
+      const uint32_t to = i < n ? place(word) : spare;
+      const float x = __uint_as_float(bits);
+      const float r = x - __uint_as_float(bits & 0xffff0000u);
+      const uint32_t rb = __float_as_uint(r);
+      const float q = r - __uint_as_float(rb & 0xffff0000u);
+      *(lds_u16 *)(size_t)(to + plane) = (uint16_t)(rb >> 16);
+      *(lds_u16 *)(size_t)(to + 2 * plane) = (uint16_t)(__float_as_uint(q) >> 16);
+    };
+    if (both) {
+#pragma unroll
+      for (int i = 0; i < STEPS; i += 2) {
+        if ((uint32_t)i < steps) {
+          rest(w[i], v[i], 16u * i + 2u * sub, at[1]);
+          rest(w[i + 1], v[i + 1], 16u * i + 2u * sub + 1u, at[1]);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < kXSteps; ++i)
+        if ((uint32_t)i < xsteps) rest(xw[i], xv[i], 16u * i + sub, at[3]);
+    }
+    for (uint32_t i = kXSteps; i < xsteps; i += 4) {
+      uint32_t y[4], z[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const auto p = __builtin_amdgcn_raw_buffer_load_b64(t.x_res, at[2] + 128u * i, 128 * u, 0);
+        y[u] = p[0];
+        z[u] = p[1];
+      }
+      low = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        high(y[u], 16u * (i + u) + sub < at[3] ? z[u] : 0u, 16u * (i + u) + sub, at[3]);
+      if (__any(low != 0)) {
+        both = true;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) rest(y[u], z[u], 16u * (i + u) + sub, at[3]);
+      }
+    }
+    return both;
+  }
+};
+
+// ---------------------------------------------------------------------------
+// Left product (Theorem 2): out[j, q] = sum over tuples of A[i, j] G[i, q].
+// A workgroup takes a batch and 128 columns of G, 16 per wave.  A wave keeps the
+// three parts of its columns of G for all tuples in registers (12 per 32 tuples)
+// and the workgroup streams the used columns of A through LDS, 32 at a time, in two
+// buffers: one is multiplied while the other is cleared and filled (by the 16-lane
+// groups, a column each, so that one barrier per chunk is enough) from entry words
+// that were loaded a chunk ahead.  So G is read once per batch and A once per 128
+// columns of G, by workgroups of one XCD that run at the same time and share it in
+// the L2.  250-row batches, vector kernel then this one: 400 image-like batches at
+// k = 300 415 -> 300 us (655 MB, 2.2 TB/s), 100 dense quantised ones at k = 200 1374 ->
+// 281 us, of which 97 the expansion.  What is left is the serial part of a chunk: two
+// waves per SIMD, whose fill (LDS writes of single values) and matrix work overlap
+// little.  One wave of a SIMD filling while the other multiplies, half a chunk apart,
+// measured 347 against 338 us; bringing the next chunk's lines into the L2 first 401.
+// Tile: [tuples / 8][32 columns] slots of 8 tuples (16 bytes), 36 slots to a row: a
+// matrix operand is one 16-byte read per lane, and a wave's writes (four columns, 32
+// tuples each) fall into different banks.
+// ---------------------------------------------------------------------------
+template <int KS>
+__global__ __launch_bounds__(kThreads) void left_mfma_kernel(
+    MfmaImg im, int64_t nb, int n_tiles, int m, const float *__restrict__ G, int64_t ldg,
+    int k, float *__restrict__ out, int64_t ldo, int accumulate) {
+  constexpr uint32_t kPlane = KS * 4 * kLeftRow + kSpare;
+  extern __shared__ __align__(16) char lds[];   // [2 buffers][3 planes][kPlane]
+  __shared__ __align__(16) Ring ring;
+  __shared__ uint32_t parts[4], bad[4], bad_g;  // of chunk c at c % 4
+  const int64_t i = blockIdx.x / kXcd;
+  const int64_t b = im.b0 + (i / n_tiles) * kXcd + blockIdx.x % kXcd;
+  if (b >= im.b0 + nb) return;
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int sub = lane % 16, grp = lane / 16;
+  const int qz = (int)(i % n_tiles) * 128;
+  const int q = qz + wave * 16 + sub;           // this lane's column of G and out
+  const Batch t = load_batch(im, b, m);
+  const float *Gb = G + t.row_base * ldg;
+  float *ob = out + b * m * ldo;
+  const int n_chunks = (int)((t.n_used + kChunk - 1) / kChunk);
+  // Columns without entries get zeros, a wave every eighth row: the first 512 with the
+  // chunks (a lane of the wave holds the column of one row), the others at the end.
+  const uint32_t n_zero = accumulate ? 0u : (uint32_t)m - t.n_used;
+  auto zero_row = [&](uint32_t j) {
+    float *o = ob + (int64_t)j * ldo + qz;
+    if (qz + lane < k) o[lane] = 0.0f;
+    if (qz + lane + kWave < k) o[lane + kWave] = 0.0f;
+  };
+  const uint32_t zr = (uint32_t)(wave + 8 * lane);
+  const uint32_t zcol = zr < n_zero ? t.order[t.n_used + zr] : 0u;
+  const uint32_t z_mine = n_zero > (uint32_t)wave ? min((n_zero - wave + 7) / 8, 64u) : 0u;
+  const uint32_t z_per = n_chunks ? (z_mine + n_chunks - 1) / n_chunks : 64u;
+  uint32_t z = 0;
+  auto zero_some = [&]() {
+    for (uint32_t e = min(z + z_per, z_mine); z < e; ++z)
+      zero_row((uint32_t)__builtin_amdgcn_readlane((int)zcol, (int)z));
+  };
+  auto zero_rest = [&]() {
+    while (z < z_mine) zero_some();
+    for (uint32_t r = 512 + wave; r < n_zero; r += 8)
+      zero_row((uint32_t)__builtin_amdgcn_readfirstlane((int)t.order[t.n_used + r]));
+  };
+  if (n_chunks == 0) zero_rest();
+  if (n_chunks == 0) return;            // (a batch without tuples has no row of G either)
+
+  if (threadIdx.x < 4) parts[threadIdx.x] = bad[threadIdx.x] = 0;
+  if (threadIdx.x == 0) bad_g = 0;
+  RingLoad index;
+  index.start(t, ring, (uint32_t)ldo * 4u);
+  const uint32_t kk = (uint32_t)(wave * 4 + grp);
+  Feed<2 * KS> feed;
+
+  // G: lane holds tuples 32 s + 8 grp .. + 7 of column q
+  u32x4 g[KS][3];
+  Range range;
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int r = 32 * s + 8 * grp + e;
+      const bool ok = r < t.n_rows && q < k;
+      const float y = Gb[ok ? (int64_t)r * ldg + q : 0];
+      x[e] = ok ? y : 0.0f;
+      range.add(__float_as_uint(x[e]));
+    }
+    split8(x, g[s]);
+  }
+  __syncthreads();
+  if (range.outside(kDenseLo, kDenseHi)) bad_g = 1;
+  feed.load(t, ring, 0, kk, sub);
+
+  const auto ores = __builtin_amdgcn_make_buffer_rsrc(
+      ob, (short)0, (int)(((int64_t)(m - 1) * ldo + k) * 4), 0x00020000);
+  const uint32_t qoff = q < k ? (uint32_t)q * 4u : 0x40000000u;   // beyond the buffer: not stored
+  uint32_t used = 3;                    // buffers (a bit each) whose planes 1 and 2 are not clear
+  // chunk c's results, stored by the wave's next half so that no wait for that half's
+  // entry words includes them
+  float res[2][4];
+  int res_chunk = -1;
+  auto put_out = [&]() {
+    if (res_chunk < 0) return;
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+      const u32x4 off = *(const tile_u32x4 *)&ring.off[res_chunk % kRing][mt * 16 + grp * 4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float r = res[mt][e];
+        if (accumulate)
+          r += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ores, off[e] + qoff, 0, 0));
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(r), ores, off[e] + qoff, 0, 0);
+      }
+    }
+    res_chunk = -1;
+  };
+  auto produce = [&](int c) {
+    if (c + 1 < n_chunks) {
+      // the group's column of chunk c + 1's buffer cleared, then the loaded words
+      // written to it (a wave's LDS operations stay in order)
+      char *tile = lds + ((c + 1) & 1) * 3 * kPlane;
+      const uint32_t bit = 1u << ((c + 1) & 1);
+#pragma unroll
+      for (int h = 0; h < KS / 4 + (KS < 4); ++h) {
+        const uint32_t rg = sub + 16u * h;
+        char *o = tile + rg * kLeftRow + kk * 16u;
+        if (KS >= 4 || rg < KS * 4) {
+          *(tile_u32x4 *)o = u32x4{0, 0, 0, 0};
+          if (used & bit) {
+            *(tile_u32x4 *)(o + kPlane) = u32x4{0, 0, 0, 0};
+            *(tile_u32x4 *)(o + 2 * kPlane) = u32x4{0, 0, 0, 0};
+          }
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+      Range vr;
+      const uint32_t base = lds_address(tile) + kk * 16u;
+      const uint32_t spare = lds_address(tile) + kPlane - kSpare + (uint32_t)lane * 4u;
+      const bool low = feed.store(t, sub, kPlane, spare, vr, [&](uint32_t word) {
+        return base + (word >> 3 & (4u * KS - 1u)) * kLeftRow + (word & 7u) * 2u;
+      });
+      used &= ~bit;
+      if (low) {
+        used |= bit;
+        parts[(c + 1) & 3] = 1;
+      }
+      if (vr.outside(kValLo, kValHi)) bad[(c + 1) & 3] = 1;
+    }
+    if (threadIdx.x == 0) parts[(c + 2) & 3] = bad[(c + 2) & 3] = 0;
+    index.step(t, ring, c, (uint32_t)ldo * 4u);
+    put_out();
+    zero_some();
+    if (c + 2 < n_chunks) {
+      feed.load(t, ring, c + 2, kk, sub);
+    }
+  };
+  auto consume = [&](int c) {
+    const char *tile = lds + (c & 1) * 3 * kPlane;
+    // the chunk's two halves of 16 columns in turn, the next operand read while the
+    // last is multiplied; lo, lo2: the small products
+    f32x4 hi[2] = {}, lo[2] = {}, lo2[2] = {};
+    const char *ta = tile + grp * kLeftRow + sub * 16;
+    auto operand = [&](int at, int plane) {
+      return *(const tile_u32x4 *)(ta + plane * kPlane + (at / 2) * (4 * kLeftRow) + (at % 2) * 256);
+    };
+    if (__builtin_amdgcn_readfirstlane((int)parts[c & 3]) == 0) {
+      u32x4 next = operand(0, 0), next2 = operand(1, 0);
+#pragma unroll
+      for (int at = 0; at < 2 * KS; ++at) {
+        const int s = at / 2, mt = at % 2;
+        const u32x4 a = next;
+        next = next2;
+        if (at + 2 < 2 * KS) next2 = operand(at + 2, 0);
+        lo[mt] = mfma(a, g[s][2], lo[mt]);
+        hi[mt] = mfma(a, g[s][0], hi[mt]);
+        lo2[mt] = mfma(a, g[s][1], lo2[mt]);
+      }
+    } else {
+      u32x4 next[3];
+#pragma unroll
+      for (int pl = 0; pl < 3; ++pl) next[pl] = operand(0, pl);
+#pragma unroll
+      for (int at = 0; at < 2 * KS; ++at) {
+        const int s = at / 2, mt = at % 2;
+        const u32x4 a1 = next[0], a2 = next[1], a3 = next[2];
+        if (at + 1 < 2 * KS) {
+#pragma unroll
+          for (int pl = 0; pl < 3; ++pl) next[pl] = operand(at + 1, pl);
+        }
+        lo[mt] = mfma(a1, g[s][2], lo[mt]);
+        hi[mt] = mfma(a1, g[s][0], hi[mt]);
+        lo2[mt] = mfma(a1, g[s][1], lo2[mt]);
+        lo[mt] = mfma(a2, g[s][1], lo[mt]);
+        lo2[mt] = mfma(a2, g[s][0], lo2[mt]);
+        lo[mt] = mfma(a3, g[s][0], lo[mt]);
+      }
+    }
+      const bool slow = __builtin_amdgcn_readfirstlane((int)(bad[c & 3] | bad_g)) != 0;
+      if (!slow) {
+        res_chunk = c;
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) res[mt][e] = hi[mt][e] + (lo[mt][e] + lo2[mt][e]);
+      } else {
+        // term by term, a wave per column and 64 columns of G at a time
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const uint32_t at = (uint32_t)c * kChunk + (uint32_t)(wave * 4 + i4);
+          if (at >= t.n_used) break;
+          const uint32_t j = t.order[at];
+          for (int h = 0; h < 128; h += kWave) {
+            const int qq = qz + h + lane;
+            const float *Gq = Gb + min(qq, k - 1);
+            float sum = 0.0f, part = 0.0f;
+            uint32_t n = 0;
+            auto term = [&](uint32_t row, float v) {
+              part = fmaf(v, Gq[(int64_t)row * ldg], part);
+              if ((++n & 15u) == 0) sum += part, part = 0.0f;
+            };
+            for (uint32_t o = t.occ[j]; o < t.occ[j + 1]; ++o)
+              term(t.ce[o] & kRowMask, __uint_as_float(t.cv[o]));
+            for (uint32_t s = t.tf[j]; s < t.tf[j + 1]; ++s) {
+              const float v = __uint_as_float(t.cv[t.tbase + s]);
+              const uint32_t y = t.tl[s], a = y < t.ni ? y : y - t.n1 + t.ni;
+              tree_rows(t, a, a + 1, [&](uint32_t row) { term(row, v); });
+            }
+            sum += part;
+            if (qq < k) {
+              float *o = ob + (int64_t)j * ldo + qq;
+              *o = accumulate ? *o + sum : sum;
+            }
+          }
+        }
+      }
+  };
+  for (int c = -1; c < n_chunks; ++c) {
+    if (c >= 0) consume(c);
+    produce(c);
+    __syncthreads();
+  }
+  put_out();
+  zero_rest();
+}
+
+// ---------------------------------------------------------------------------
+// Right product (Theorem 1): R[i, q] = sum over used columns of A[i, j] W[j, q].
+// A workgroup takes a batch and N = 16 NF (8 / WM) columns of W and keeps that
+// part of R in registers (a wave: 64 tuples x 16 NF columns); the used columns of A
+// and the rows of W they name stream through LDS, 32 at a time, double-buffered as
+// in the left product.  W is split into its parts on the way (it stays in the L2).
+// 400 image-like batches at k = 300 381 -> 255 us, 100 dense quantised ones at k = 200
+// 1275 -> 262 us.  NF = 5 (two tiles instead of three at k = 300) spills: 434 us.
+// Tiles: A [8][64 WM tuples] slots of 4 columns (8 bytes), W [4][N] slots of 8 rows; a
+// wave owns the 4 columns of one slot row, which it clears and fills by itself.
+// ---------------------------------------------------------------------------
+template <int WM, int NF>
+__global__ __launch_bounds__(kThreads) void right_mfma_kernel(
+    MfmaImg im, int64_t nb, int n_tiles, int m, const float *__restrict__ W, int64_t ldw,
+    int k, float *__restrict__ R, int64_t ldr) {
+  constexpr int kRows = 64 * WM, kWn = 8 / WM, N = 16 * NF * kWn;
+  constexpr int kSteps = kRows / 16;
+  constexpr uint32_t kPlane = 4 * kRows * 16 + kSpare, kBPlane = 4 * N * 16;
+  constexpr int kTasks = (4 * N + kThreads - 1) / kThreads;   // slots of W per thread
+  extern __shared__ __align__(16) char lds[];          // A [2][3][kPlane], W [2][3][kBPlane]
+  __shared__ __align__(16) Ring ring;
+  __shared__ uint32_t parts[4], bad;     // parts of chunk c at c % 4
+  const int64_t i = blockIdx.x / kXcd;
+  const int64_t b = im.b0 + (i / n_tiles) * kXcd + blockIdx.x % kXcd;
+  if (b >= im.b0 + nb) return;
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int sub = lane % 16, grp = lane / 16;
+  const int wm = wave % WM, wn = wave / WM;
+  const int q0 = (int)(i % n_tiles) * N;
+  const Batch t = load_batch(im, b, m);
+  const int n_chunks = (int)((t.n_used + kChunk - 1) / kChunk);
+  const auto wres = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float *>(W), (short)0, (int)(((int64_t)(m - 1) * ldw + k) * 4), 0x00020000);
+  char *ldsB = lds + 6 * kPlane;
+
+  if (threadIdx.x < 4) parts[threadIdx.x] = 0;
+  if (threadIdx.x == 0) bad = 0;
+  const uint32_t kk = (uint32_t)(wave * 4 + grp);   // this group's column within a chunk
+  RingLoad index;
+  index.start(t, ring, (uint32_t)ldw * 4u);
+  Feed<kSteps> feed;
+
+  float w[kTasks][8];
+  Range range;
+  auto load_w = [&](int c) {
+#pragma unroll
+    for (int e = 0; e < kTasks; ++e) {
+      const int task = threadIdx.x + e * kThreads;
+      if (task < 4 * N) {
+        const uint32_t n = (uint32_t)(task % N);
+        const uint32_t *rows = ring.off[c % kRing] + 8 * (task / N);
+        // a row that is not there, or a column beyond k: outside the buffer, read as 0
+        const uint32_t off = q0 + (int)n < k ? (uint32_t)(q0 + n) * 4u : 0x40000000u;
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+          w[e][r] =
+              __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wres, rows[r] + off, 0, 0));
+      }
+    }
+  };
+  auto store_w = [&](int c) {
+    char *tile = ldsB + (c & 1) * 3 * kBPlane;
+#pragma unroll
+    for (int e = 0; e < kTasks; ++e) {
+      const int task = threadIdx.x + e * kThreads;
+      if (task < 4 * N) {
+        u32x4 p[3];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) range.add(__float_as_uint(w[e][r]));
+        split8(w[e], p);
+#pragma unroll
+        for (int s = 0; s < 3; ++s) *(u32x4 *)(tile + s * kBPlane + task * 16) = p[s];
+      }
+    }
+  };
+  bool out_of_range = false;
+  f32x4 acc[4][NF] = {};
+  uint32_t used = 3;                     // buffers whose planes 1 and 2 are not clear
+  auto produce = [&](int c) {
+    if (c + 1 < n_chunks) {
+      char *tile = lds + ((c + 1) & 1) * 3 * kPlane + wave * (kRows * 8);
+      const uint32_t bit = 1u << ((c + 1) & 1);
+#pragma unroll
+      for (int o = 0; o < kRows * 8; o += kWave * 16) {
+        if (kRows * 8 >= kWave * 16 || lane * 16 < kRows * 8) {
+          *(tile_u32x4 *)(tile + o + lane * 16) = u32x4{0, 0, 0, 0};
+          if (used & bit) {
+            *(tile_u32x4 *)(tile + kPlane + o + lane * 16) = u32x4{0, 0, 0, 0};
+            *(tile_u32x4 *)(tile + 2 * kPlane + o + lane * 16) = u32x4{0, 0, 0, 0};
+          }
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+      Range vr;
+      const uint32_t base = lds_address(tile) + (uint32_t)grp * 2u;
+      const uint32_t spare = lds_address(lds) + ((c + 1) & 1) * 3 * kPlane + kPlane - kSpare +
+                             (uint32_t)lane * 4u;
+      const bool low = feed.store(t, sub, kPlane, spare, vr, [&](uint32_t word) {
+        return base + (word & (kRows - 1u)) * 8u;
+      });
+      used &= ~bit;
+      if (low) {
+        used |= bit;
+        parts[(c + 1) & 3] = 1;
+      }
+      out_of_range |= vr.outside(kValLo, kValHi);
+      store_w(c + 1);
+    }
+    if (threadIdx.x == 0) parts[(c + 2) & 3] = 0;
+    index.step(t, ring, c, (uint32_t)ldw * 4u);
+    if (c + 2 < n_chunks) {
+      load_w(c + 2);
+      feed.load(t, ring, c + 2, kk, sub);
+    }
+  };
+  auto consume = [&](int c) {
+    // lane (sub, grp): columns 8 grp .. + 7 of a tuple, in two slots
+    const char *ta = lds + (c & 1) * 3 * kPlane + (2 * grp * kRows + wm * 64 + sub) * 8;
+    const char *tb = ldsB + (c & 1) * 3 * kBPlane + (grp * N + wn * 16 * NF + sub) * 16;
+    auto load_a = [&](int s, int x) {
+      const u32x2 l = *(const tile_u32x2 *)(ta + s * kPlane + x * 128);
+      const u32x2 h = *(const tile_u32x2 *)(ta + s * kPlane + x * 128 + kRows * 8);
+      return u32x4{l[0], l[1], h[0], h[1]};
+    };
+    if (__builtin_amdgcn_readfirstlane((int)parts[c & 3]) == 0) {
+      u32x4 a[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) a[x] = load_a(0, x);
+      u32x4 next[3];
+#pragma unroll
+      for (int s = 0; s < 3; ++s) next[s] = *(const tile_u32x4 *)(tb + s * kBPlane);
+#pragma unroll
+      for (int n = 0; n < NF; ++n) {
+        u32x4 w3[3];
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+          w3[s] = next[s];
+          if (n + 1 < NF) next[s] = *(const tile_u32x4 *)(tb + s * kBPlane + (n + 1) * 256);
+        }
+        f32x4 sum[4] = {};
+#pragma unroll
+        for (int s = 2; s >= 0; --s)
+#pragma unroll
+          for (int x = 0; x < 4; ++x) sum[x] = mfma(a[x], w3[s], sum[x]);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) acc[x][n] += sum[x];
+      }
+    } else {
+#pragma unroll
+      for (int xh = 0; xh < 4; xh += 2) {
+        u32x4 a[2][3];
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int s = 0; s < 3; ++s) a[x][s] = load_a(s, xh + x);
+#pragma unroll
+        for (int n = 0; n < NF; ++n) {
+          u32x4 w3[3];
+#pragma unroll
+          for (int s = 0; s < 3; ++s) w3[s] = *(const tile_u32x4 *)(tb + s * kBPlane + n * 256);
+          f32x4 sum[2] = {};
+#pragma unroll
+          for (int x = 0; x < 2; ++x) sum[x] = mfma(a[x][2], w3[0], sum[x]);
+#pragma unroll
+          for (int x = 0; x < 2; ++x) sum[x] = mfma(a[x][1], w3[1], sum[x]);
+#pragma unroll
+          for (int x = 0; x < 2; ++x) sum[x] = mfma(a[x][0], w3[2], sum[x]);
+#pragma unroll
+          for (int x = 0; x < 2; ++x) sum[x] = mfma(a[x][1], w3[0], sum[x]);
+#pragma unroll
+          for (int x = 0; x < 2; ++x) sum[x] = mfma(a[x][0], w3[1], sum[x]);
+#pragma unroll
+          for (int x = 0; x < 2; ++x) sum[x] = mfma(a[x][0], w3[0], sum[x]);
+#pragma unroll
+          for (int x = 0; x < 2; ++x) acc[xh + x][n] += sum[x];
+          __builtin_amdgcn_sched_barrier(0);   // (loads hoisted further ahead spill)
+        }
+      }
+    }
+  };
+  __syncthreads();
+  if (n_chunks) {
+    load_w(0);
+    feed.load(t, ring, 0, kk, sub);
+  }
+  for (int c = n_chunks ? -1 : 0; c < n_chunks; ++c) {
+    if (c >= 0) consume(c);
+    produce(c);
+    __syncthreads();
+  }
+  if (out_of_range || range.outside(kDenseLo, kDenseHi)) bad = 1;
+  __syncthreads();
+  float *Rb = R + t.row_base * ldr;
+  if (!bad) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = wm * 64 + x * 16 + grp * 4 + e;
+#pragma unroll
+        for (int n = 0; n < NF; ++n) {
+          const int q = q0 + (wn * NF + n) * 16 + sub;
+          if (r < t.n_rows && q < k) Rb[(int64_t)r * ldr + q] = acc[x][n][e];
+        }
+      }
+    }
+    return;
+  }
+  // term by term: a wave per tuple, each code's chain walked to the root
+  const toc_batch *bp = im.batches + b;
+  const uint32_t *span = im.span + uniform64(bp->span_base);
+  const uint32_t *D = im.dcodes + uniform64(bp->d_base);
+  const toc_key *key = im.key + uniform64(bp->code_base);
+  const toc_link *link = im.link + (uniform64(bp->deep_base) - (int64_t)t.n1);
+  for (int r = wave; r < t.n_rows; r += kThreads / kWave) {
+    for (int h = 0; h < N; h += kWave) {
+      const int q = q0 + h + lane;
+      const float *Wq = W + min(q, k - 1);
+      float sum = 0.0f, part = 0.0f;
+      uint32_t n = 0;
+      for (uint32_t e = span[r]; e < span[r + 1]; ++e) {
+        for (uint32_t c = D[e];;) {
+          const toc_key y = key[c];
+          part = fmaf(y.val, Wq[(int64_t)y.col * ldw], part);
+          if ((++n & 15u) == 0) sum += part, part = 0.0f;
+          if (c < t.n1) break;
+          c = link[c].parent;
+        }
+      }
+      if (h + lane < N && q < k) Rb[(int64_t)r * ldr + q] = sum + part;
+    }
+  }
+}
+
+MfmaImg image_of(const toc_dev *d) {
+  const uint8_t *p = (const uint8_t *)d->buf;
+  const toc_layout &L = d->layout;
+  MfmaImg im{};
+  im.batches = (const toc_batch *)(p + L.batches);
+  im.key = (const toc_key *)(p + L.key);
+  im.link = (const toc_link *)(p + L.link);
+  im.span = (const uint32_t *)(p + L.span);
+  im.dcodes = (const uint32_t *)(p + L.dcodes);
+  im.centry = (const uint32_t *)(p + L.centry);
+  im.cval = (const uint32_t *)(p + L.cval);
+  im.occ_off = (const uint32_t *)(p + L.occ_off);
+  im.tlist = (const uint32_t *)(p + L.tlist);
+  im.cols = (const uint32_t *)(p + L.cols);
+  im.tchild = (const uint32_t *)(p + L.tchild);
+  return im;
+}
+
+// Workspace of a run of batches: the expanded pairs per column (m words a batch,
+// rounded up to 16 bytes), then room for a pair in every cell of every batch.
+size_t counters_bytes(int64_t n, int64_t m) { return (size_t)(n * ((m + 3) / 4 * 16)); }
+size_t pass_bytes(const toc_dev *d, int64_t n) {
+  const int64_t m = d->info.n_cols;
+  return counters_bytes(n, m) + (size_t)(8 * n * m * d->max_rows);
+}
+constexpr size_t kPassBytes = (size_t)1 << 30;   // workspace asked for at most
+constexpr size_t kLeastBytes = (size_t)32 << 20;   // holds any batch; less is not used
+
+// Per pass of batches: their tree codes expanded into the workspace, then `kernel`
+// over all (batch, tile) pairs, the tiles of a batch on one XCD.
+template <typename K, typename... Args>
+toc_status run(const char *name, K kernel, size_t lds, const toc_dev *d, int n_tiles, void *ws,
+               size_t ws_bytes, hipStream_t s, Args... args) {
+  if (hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)lds) != hipSuccess)
+    return fail(TOC_EDEVICE, "cannot raise dynamic LDS to %zu bytes", lds);
+  const int64_t nb = d->info.n_batches, m = d->info.n_cols;
+  for (int64_t b0 = 0; b0 < nb;) {
+    const int blocks =
+        (int)std::max<int64_t>(1, std::min<int64_t>(64, (d->max_tree + kExpandThreads - 1) / kExpandThreads));
+    const int64_t most = std::max<int64_t>(1, ((int64_t)1 << 21) / std::max(blocks, n_tiles));
+    const int64_t n = std::min({nb - b0, most, (int64_t)(ws_bytes / pass_bytes(d, 1))});
+    MfmaImg im = image_of(d);
+    im.b0 = b0;
+    im.n_stride = (m + 3) / 4 * 4;
+    im.x_stride = m * d->max_rows;
+    uint32_t *xn = (uint32_t *)ws;
+    uint2 *xpair = (uint2 *)((uint8_t *)ws + counters_bytes(n, m));
+    im.xn = xn;
+    im.xpair = xpair;
+    const int64_t zeros = (int64_t)(counters_bytes(n, m) / 16);
+    hipLaunchKernelGGL(tree_zero_kernel, dim3((unsigned)((zeros + 255) / 256)), dim3(256), 0, s,
+                       (u32x4 *)xn, zeros);
+    hipLaunchKernelGGL(tree_expand_kernel, dim3((unsigned)(n * blocks)), dim3(kExpandThreads), 0, s,
+                       im, (int)m, blocks, xn, xpair);
+    const unsigned grid = (unsigned)((n + kXcd - 1) / kXcd * kXcd * n_tiles);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, s, im, n, n_tiles, args...);
+    b0 += n;
+  }
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return fail(TOC_EDEVICE, "%s: %s", name, hipGetErrorString(e));
+  return TOC_OK;
+}
+
+}  // namespace
+
+namespace toc {
+
+// Where these kernels are the faster ones.  Against the vector kernels of
+// toc_device.hip (right / left, us, vector then matrix; 250-row batches):
+//  - dense quantised batches, whose many deep codes cost those a table row each:
+//    always (100 batches, k = 200: 1277 -> 266, 1404 -> 291; one batch, k = 8: 317 -> 132,
+//    469 -> 188).  A right product of batches with far fewer codes than nonzeros
+//    runs on the codes instead (400 census batches, k = 20: 122 against 265);
+//  - others (image-like, one-hot): when the pairs of batches and 64-column tiles fill
+//    the chip and more than one tile shares a batch's expansion (400 image-like
+//    batches, k = 300: 400 -> 244, 440 -> 302; 64 batches: 106 -> 60, 115 -> 66; but 64
+//    batches at k = 128: 56 and 61 against 56 and 64, 400 batches of 100 rows at k = 20:
+//    35 and 61 against 63 and 81);
+//  - right products of 2 and 3 columns, which only the general kernel took (400
+//    image-like batches, k = 2: 2368 -> 80).
+// Below a sixteenth of the tiles' cells filled (sparse text) the expansion is mostly zeros.
+bool mfma_suits(const toc_dev *d, int32_t k, bool right) {
+  const toc_dev_info &n = d->info;
+  if (k < 2 || d->max_rows > 256 || d->max_ucols < 1) return false;
+  if (pass_bytes(d, 1) > kLeastBytes) return false;
+  const int64_t cells = n.n_rows * d->max_ucols;
+  if (n.nnz * 16 < cells) return false;
+  if (right && k < 4) return true;
+  if (right && n.n_codes * 10 < n.nnz * 9) return false;
+  if (n.nnz * 2 >= cells && n.n_deep * 32 > n.n_stored) return true;
+  return k > 64 && n.n_batches * ((k + 63) / 64) >= 300;
+}
+
+size_t mfma_workspace(const toc_dev *d) {
+  return std::min(pass_bytes(d, d->info.n_batches), kPassBytes);
+}
+
+bool mfma_fits(const toc_dev *d, int32_t k, bool right, int64_t ld, const void *ws,
+               size_t ws_bytes) {
+  // 32-bit byte offsets into W and a batch's block of out
+  if (!mfma_suits(d, k, right) || (int64_t)d->info.n_cols * ld >= ((int64_t)1 << 28)) return false;
+  return ws && ((uintptr_t)ws & 15) == 0 && ws_bytes >= std::min(mfma_workspace(d), kLeastBytes);
+}
+
+toc_status left_mfma(const toc_dev *d, const float *G, int32_t k, int64_t ldg, float *out, int64_t ldo,
+                     int32_t accumulate, void *ws, size_t ws_bytes, void *stream) {
+  hipStream_t s = (hipStream_t)stream;
+  const int n_tiles = (k + 127) / 128;
+  const int ks = d->max_rows <= 64 ? 2 : d->max_rows <= 128 ? 4 : 8;
+  const size_t lds = (size_t)6 * (ks * 4 * kLeftRow + kSpare);
+  const int m = d->info.n_cols;
+#define TOC_LM(KS)                                                                              \
+  return run("left_mfma_kernel", left_mfma_kernel<KS>, lds, d, n_tiles, ws, ws_bytes, s, m, G, ldg, \
+             (int)k, out, ldo, (int)accumulate)
+  if (ks == 2) TOC_LM(2);
+  if (ks == 4) TOC_LM(4);
+  TOC_LM(8);
+#undef TOC_LM
+}
+
+toc_status right_mfma(const toc_dev *d, const float *W, int32_t k, int64_t ldw, float *R, int64_t ldr,
+                      void *ws, size_t ws_bytes, void *stream) {
+  hipStream_t s = (hipStream_t)stream;
+  const int wm = d->max_rows <= 64 ? 1 : d->max_rows <= 128 ? 2 : 4;
+  const int wn = 8 / wm, most = wm == 1 ? 2 : 4;
+  const int nf = (k + 15) / 16;
+  const int n_tiles = (nf + wn * most - 1) / (wn * most);
+  const int f = (nf + wn * n_tiles - 1) / (wn * n_tiles);
+  const size_t lds = (size_t)6 * (4 * 16 * (64 * wm + 16 * f * wn) + kSpare);
+  const int m = d->info.n_cols;
+#define TOC_RM(WM, NF)                                                                          \
+  if (wm == WM && f == NF)                                                                      \
+    return run("right_mfma_kernel", right_mfma_kernel<WM, NF>, lds, d, n_tiles, ws, ws_bytes, s, m, W, \
+               ldw, (int)k, R, ldr)
+  TOC_RM(4, 1);
+  TOC_RM(4, 2);
+  TOC_RM(4, 3);
+  TOC_RM(4, 4);
+  TOC_RM(2, 1);
+  TOC_RM(2, 2);
+  TOC_RM(2, 3);
+  TOC_RM(2, 4);
+  TOC_RM(1, 1);
+  TOC_RM(1, 2);
+#undef TOC_RM
+  return fail(TOC_EINVAL, "no right_mfma_kernel for %d fragments", f);
+}
+
+}  // namespace toc

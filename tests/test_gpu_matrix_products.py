@@ -1,0 +1,191 @@
+"""Products with k >= 2 on the matrix cores: against the oracle at the edges of their
+tiles (16 and 128 columns, 32 columns of A, 64 / 128 / 256 tuples), on batches whose
+tree codes need several levels, and with operands that send them term by term.
+
+Bound: |gpu - oracle| <= 1e-5 * S per element, S the sum of the absolute terms: the
+parts' dropped products and the sums' roundings stay below it for any of these
+sizes (at most 256 terms beside the 2^-22 of a product).
+"""
+
+import numpy as np
+import pytest
+
+import oracle as O
+import paper_1702_06943_amd as T
+from workloads import Batches, tiny_batch
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+TOL = 1e-5
+
+
+def _batches(rows_list, cols, seed, **kw):
+    parts = []
+    for i, n in enumerate(rows_list):
+        rp, c, v = tiny_batch(seed + i, n, cols, **kw)
+        parts.append(Batches(cols, [n], rp, c, v))
+    return Batches.concat(parts)
+
+
+def _upload(B, flags=0):
+    encs = T.toc_encode_batches(B.n_rows, B.n_cols, B.rowptr, B.col, B.val)
+    buf = torch.empty(T.toc_upload_size(encs, flags), dtype=torch.uint8, device=DEV)
+    return T.toc_upload(encs, buf, flags)
+
+
+def _ws(dev, op, k):
+    n, _ = T.toc_workspace_size(dev, op, k)
+    return torch.full((max(n, 4) // 4,), float("nan"), device=DEV)
+
+
+def _asks_for_expansion(dev, op, k):
+    """The matrix-core path is the only one whose workspace covers every cell."""
+    info = T.toc_dev_info_get(dev)
+    return T.toc_workspace_size(dev, op, k)[0] >= 8 * info["n_rows"] * info["n_cols"]
+
+
+def _rows(B, b):
+    n, rp, c, v = B.batch(b)
+    return O.canonicalize(n, B.n_cols, rp, c, v)
+
+
+def _check_right(B, R, W):
+    for b in range(B.n_batches):
+        r0, r1 = int(B.row_off[b]), int(B.row_off[b + 1])
+        ref, S = O.dense_right(_rows(B, b), B.n_cols, W)
+        assert np.all(np.abs(R[r0:r1] - ref) <= TOL * S), f"batch {b}"
+
+
+def _check_left(B, out, G, init=None):
+    m = B.n_cols
+    for b in range(B.n_batches):
+        r0, r1 = int(B.row_off[b]), int(B.row_off[b + 1])
+        ref, S = O.dense_left(_rows(B, b), m, G[r0:r1])
+        got = out[b * m:(b + 1) * m].astype(np.float64)
+        if init is not None:
+            ref = ref + init[b * m:(b + 1) * m]
+            S = S + np.abs(init[b * m:(b + 1) * m])
+        assert np.all(np.abs(got - ref) <= TOL * S), f"batch {b}"
+
+
+@pytest.mark.parametrize("rows,cols,k,kw", [
+    ([1, 64, 40], 5, 2, dict(density=0.9, n_values=3, prefix_copy=0.6)),
+    ([64, 63], 33, 16, dict(density=0.9, n_values=3, prefix_copy=0.6)),
+    ([65, 128], 32, 17, dict(density=0.8, n_values=4, prefix_copy=0.5)),
+    ([129, 7, 200], 70, 130, dict(density=0.9, n_values=6, prefix_copy=0.5)),
+    ([256, 0, 255], 97, 300, dict(density=0.7, n_values=5, prefix_copy=0.5)),
+    ([250], 64, 128, dict(density=1.0, n_values=2, prefix_copy=0.9)),
+    ([250, 31], 40, 20, dict(density=0.9, n_values=3, prefix_copy=0.6, integer=True)),
+])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_left(rows, cols, k, kw, accumulate):
+    B = _batches(rows, cols, 7000 + cols, **kw)
+    dev = _upload(B)
+    assert _asks_for_expansion(dev, T.TOC_OP_LEFT, k)
+    rng = np.random.default_rng(cols * k)
+    G = rng.standard_normal((int(B.row_off[-1]), k)).astype(np.float32)
+    Gd = torch.zeros((len(G), k + 3), device=DEV)
+    Gd[:, :k] = torch.from_numpy(G)
+    init = rng.standard_normal((B.n_batches * cols, k)).astype(np.float32)
+    out = torch.full((len(init), k + 5), float("nan"), device=DEV)
+    out[:, :k] = torch.from_numpy(init)
+    T.toc_left_mul(dev, Gd[:, :k], out[:, :k], accumulate, _ws(dev, T.TOC_OP_LEFT, k))
+    _check_left(B, out[:, :k].cpu().numpy(), G, init if accumulate else None)
+    assert torch.isnan(out[:, k:]).all()          # the padding stays untouched
+    # the same bits without a workspace of the caller's
+    again = torch.zeros((len(init), k), device=DEV)
+    again += torch.from_numpy(init).to(DEV)
+    T.toc_left_mul_noalloc(dev, Gd[:, :k], again, accumulate)
+    assert torch.equal(again, out[:, :k].contiguous())
+
+
+@pytest.mark.parametrize("rows,cols,k,kw", [
+    ([1, 64, 40], 5, 2, dict(density=0.9, n_values=3, prefix_copy=0.6)),
+    ([65, 128, 1], 33, 3, dict(density=0.5, n_values=4, prefix_copy=0.5)),
+    ([129, 0, 256], 96, 3, dict(density=0.3, n_values=50, prefix_copy=0.3)),
+    ([20, 64] * 55, 40, 150, dict(density=0.6, n_values=400, prefix_copy=0.0)),
+    ([128, 30] * 30, 65, 257, dict(density=0.7, n_values=900, prefix_copy=0.0)),
+    ([250, 256, 131] * 25, 31, 200, dict(density=0.9, n_values=2000, prefix_copy=0.0)),
+    ([250, 17] * 30, 50, 300, dict(density=0.8, n_values=3000, prefix_copy=0.02)),
+])
+def test_right(rows, cols, k, kw):
+    B = _batches(rows, cols, 8000 + cols, **kw)
+    dev = _upload(B)
+    assert _asks_for_expansion(dev, T.TOC_OP_RIGHT, k)
+    W = np.random.default_rng(cols * k).standard_normal((cols, k)).astype(np.float32)
+    Wd = torch.zeros((cols, k + 2), device=DEV)
+    Wd[:, :k] = torch.from_numpy(W)
+    R = torch.full((int(B.row_off[-1]), k + 1), float("nan"), device=DEV)
+    T.toc_right_mul(dev, Wd[:, :k], R[:, :k], _ws(dev, T.TOC_OP_RIGHT, k))
+    _check_right(B, R[:, :k].cpu().numpy(), W)
+    assert torch.isnan(R[:, k:]).all()
+
+
+def test_dead_codes_and_small_workspace():
+    """An image that keeps unused codes, and a workspace too small for the expansion
+    (the general kernels take the call)."""
+    B = _batches([200, 90], 45, 8800, density=0.9, n_values=3, prefix_copy=0.6)
+    k = 20
+    G = np.random.default_rng(1).standard_normal((290, k)).astype(np.float32)
+    Gd = torch.from_numpy(G).to(DEV)
+    for flags in (0, T.TOC_UPLOAD_KEEP_DEAD):
+        dev = _upload(B, flags)
+        n, least = T.toc_workspace_size(dev, T.TOC_OP_LEFT, k)
+        for size in (n, least):
+            out = torch.full((2 * 45, k), float("nan"), device=DEV)
+            ws = torch.empty(size, dtype=torch.uint8, device=DEV) if size else None
+            T.toc_left_mul(dev, Gd, out, False, ws)
+            _check_left(B, out.cpu().numpy(), G)
+
+
+@pytest.mark.parametrize("bad", [np.inf, np.nan, 1e-30, 1e30, 3e38])
+def test_operands_outside_the_split(bad):
+    """A non-finite or extreme entry of W or G reaches only what it multiplies."""
+    k = 2
+    B = _batches([70, 130], 37, 8900, density=0.6, n_values=6, prefix_copy=0.4)
+    dev = _upload(B)
+    assert _asks_for_expansion(dev, T.TOC_OP_RIGHT, k)
+    rng = np.random.default_rng(5)
+    W = rng.standard_normal((37, k)).astype(np.float32)
+    G = rng.standard_normal((200, k)).astype(np.float32)
+    W[4, 1] = bad
+    G[9, 0] = bad
+    G[150] = bad
+    R = torch.empty((200, k), device=DEV)
+    out = torch.empty((2 * 37, k), device=DEV)
+    T.toc_right_mul(dev, torch.from_numpy(W).to(DEV), R, _ws(dev, T.TOC_OP_RIGHT, k))
+    T.toc_left_mul(dev, torch.from_numpy(G).to(DEV), out, False, _ws(dev, T.TOC_OP_LEFT, k))
+    R, out = R.cpu().numpy(), out.cpu().numpy()
+    for b in range(2):
+        r0, r1 = int(B.row_off[b]), int(B.row_off[b + 1])
+        A = np.zeros((r1 - r0, 37))
+        n, rp, c, v = B.batch(b)
+        for i in range(n):
+            A[i, c[rp[i]:rp[i + 1]]] = v[rp[i]:rp[i + 1]]
+        for got, X, Y in ((R[r0:r1], A, W), (out[b * 37:(b + 1) * 37], A.T, G[r0:r1])):
+            Y = Y.astype(np.float64)
+            held = (X != 0).astype(np.float64) @ (~np.isfinite(Y)).astype(np.float64) > 0
+            safe = np.where(np.isfinite(Y), Y, 0)
+            ref, S = X @ safe, np.abs(X) @ np.abs(safe)
+            ok = ~held & (S < 1e38)
+            assert np.all(np.abs(got - ref)[ok] <= TOL * S[ok])
+            assert not np.isfinite(got[held]).any()
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -40, 2.0 ** 55])
+def test_values_outside_the_split(scale):
+    B = _batches([66, 40], 35, 8950, density=0.9, n_values=5, prefix_copy=0.5)
+    B.val = (B.val * np.float32(scale)).astype(np.float32)
+    dev = _upload(B)
+    k = 3
+    rng = np.random.default_rng(6)
+    W = rng.standard_normal((35, k)).astype(np.float32)
+    G = rng.standard_normal((106, k)).astype(np.float32)
+    R = torch.empty((106, k), device=DEV)
+    out = torch.empty((70, k), device=DEV)
+    T.toc_right_mul(dev, torch.from_numpy(W).to(DEV), R, _ws(dev, T.TOC_OP_RIGHT, k))
+    T.toc_left_mul(dev, torch.from_numpy(G).to(DEV), out, False, _ws(dev, T.TOC_OP_LEFT, k))
+    _check_right(B, R.cpu().numpy(), W)
+    _check_left(B, out.cpu().numpy(), G)
