@@ -8,9 +8,11 @@
 // entry leaves its pair's node index (1..|I|) in the D slot of its position.
 //
 // Phase II (greedy longest matches, one new node after every match that does not
-// end its tuple) is sequential inside a batch by nature: the tree a tuple matches
-// against is the one the earlier tuples grew.  One lane runs one batch, so a wave
-// walks 64 batches at once; the children of each tree node live in a per-lane
+// end its tuple) goes tuple by tuple, as the tree a tuple matches against is the one
+// the earlier tuples grew, but is parallel inside a tuple: a code's sequence begins at a
+// pair that its tuple holds once, so no node that a tuple adds can be matched by the
+// rest of the same tuple, and the longest matches from all its entries can be looked
+// up at once.  One workgroup runs one batch; the children of its tree nodes live in an
 // open-addressing table keyed by (node, pair node index).  A node's extension by a
 // pair is a child of the node keyed by that pair, so the pair's first-layer node
 // index stands for the pair in the key.  The codes are written over the pair
@@ -28,9 +30,10 @@ namespace {
 constexpr int kEpBlock = 256;               // phase I workgroup
 constexpr int kEpWave = 64;
 constexpr int kEpWaves = kEpBlock / kEpWave;
-constexpr int kEtBlock = 64;                // phase II: one wave per workgroup
+constexpr int kEtBlock = 256;               // phase II workgroup: entries of a tuple at a time
+constexpr int kEtWaves = kEtBlock / kEpWave;
 constexpr int64_t kMaxPairGroups = 1024;    // phase I workgroups (each owns a table)
-constexpr int64_t kMaxLanes = 16384;        // phase II lanes (each owns a table)
+constexpr int64_t kMaxLanes = 16384;        // phase II workgroups (each owns a table)
 constexpr int64_t kTableBudget = (int64_t)8 << 30;   // bytes for each phase's tables
 constexpr uint64_t kEmptyKey = ~0ull;
 constexpr uint32_t kNone = 0xFFFFFFFFu;
@@ -43,12 +46,10 @@ struct PairSlot {
   uint32_t node;
 };
 
-// Phase II slot: (parent node << 32 | pair node index) -> child node; `tag` is the
-// batch that wrote it, so a lane's table needs no clearing between its batches.
+// Phase II slot: (parent node << 32 | pair node index) -> child node.
 struct ChildSlot {
   uint64_t key;
-  uint32_t child;
-  uint32_t tag;
+  uint64_t child;
 };
 
 // Slots of a table for up to n keys: a power of two at least 1.5 n (and 64).
@@ -78,6 +79,16 @@ __device__ inline uint32_t load_agent(const uint32_t *p) {
 }
 __device__ inline int64_t load_agent64(const int64_t *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline uint64_t load_agent64(const uint64_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A workgroup barrier after which the global stores and atomics of all its waves have
+// been performed at the L2 (the loads of load_agent read there).
+__device__ inline void barrier_global() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
 }
 
 // Exclusive prefix sum of x over the workgroup; total gets the sum of all.
@@ -244,63 +255,155 @@ __global__ __launch_bounds__(kEpBlock) void enc_pairs_kernel(
   }
 }
 
-// Phase II: lane g runs batches g, g + n_lanes, ...
+// Phase II: workgroup g runs batches g, g + gridDim.x, ...
+//
+// Bound by the latency of the table probes, which miss the L2 (a megabyte per
+// image-like batch): a tuple takes as many dependent probes as its longest match has
+// pairs, plus one to insert its new nodes, where one lane per batch took one per pair.
+// 256 image-like batches (39,200 pairs each) took 78 ms that way, 1.5 ms now; a larger
+// workgroup gains nothing (157 entries a tuple), more batches run side by side.
 __global__ __launch_bounds__(kEtBlock) void enc_tuples_kernel(
     const int64_t *__restrict__ rowptr, const int64_t *__restrict__ row_off, int64_t n_batches,
-    int64_t n_lanes, ChildSlot *__restrict__ tables, int64_t table_stride, uint32_t *D,
+    ChildSlot *__restrict__ tables, int64_t table_stride, uint32_t *D,
     int64_t *__restrict__ D_rowptr, int64_t *__restrict__ counts,
     const int32_t *__restrict__ status) {
-  const int64_t g = (int64_t)blockIdx.x * kEtBlock + threadIdx.x;
-  if (g >= n_lanes) return;
+  __shared__ uint32_t pairs[2 * kEtBlock];     // pair nodes from the segment's start on
+  __shared__ uint32_t len[kEtBlock];           // longest match from each entry
+  __shared__ uint64_t multi[kEtWaves], take[kEtWaves];   // entries with len > 1; codes' first entries
+  __shared__ uint32_t ends[kEtBlock], after;   // tuple ends; where the last match ends
+  const int tid = threadIdx.x, lane = tid % kEpWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kEpWave);
   const int64_t base = rowptr[0];
-  uint4 *slots4 = (uint4 *)(tables + g * table_stride);   // (key lo, key hi, child, tag)
-  for (int64_t b = g; b < n_batches; b += n_lanes) {
+  ChildSlot *tab = tables + blockIdx.x * table_stride;
+  for (int64_t b = blockIdx.x; b < n_batches; b += gridDim.x) {
     if (status[b] != 0) continue;
-    const int64_t r0 = row_off[b], r1 = row_off[b + 1];
+    const int64_t r0 = row_off[b], n_rows = row_off[b + 1] - r0;
     const int64_t e0 = rowptr[r0] - base;
-    const uint32_t mask = table_slots_dev((uint32_t)(rowptr[r1] - base - e0)) - 1;
-    const uint32_t tag = (uint32_t)b;
-    uint32_t next = (uint32_t)counts[4 * b] + 1;     // next node index (Algorithm 1's AddNode)
-    int64_t q = e0;                                    // where the next code goes
+    const uint32_t slots = table_slots_dev((uint32_t)(rowptr[r0 + n_rows] - base - e0));
+    const uint32_t mask = slots - 1;
+    for (uint32_t s = tid; s < slots; s += kEtBlock) tab[s].key = kEmptyKey;
+    uint32_t *Db = D + e0;                     // the batch's pair nodes, then its codes
     int64_t *drp = D_rowptr + r0 + b;
-    int64_t start = e0;                                // tuple starts among the nonzeros
-    for (int64_t i = 0; i < r1 - r0; ++i) {
-      const int64_t end = e0 + drp[i + 1];
-      drp[i] = q - e0;
-      int64_t p = start;
-      start = end;
-      if (p == end) continue;
-      // longest matches from the tree; n is the match so far, pc the pair of entry p
-      // (as its first-layer node), pn the pair after it, loaded ahead of the probe
-      uint32_t n = D[p++];
-      uint32_t pc = p < end ? D[p] : 0u;
-      while (p < end) {
-        // one 16-byte load per probed slot, issued ahead of the next pair's load
-        const uint64_t key = ((uint64_t)n << 32) | pc;
-        uint32_t s = mix64(key) & mask;
-        uint4 v = slots4[s];
-        const uint32_t pn = D[p + 1 < end ? p + 1 : p];   // used only when p + 1 < end
-        while (true) {
-          const bool own = v.w == tag, same = ((v.x ^ (uint32_t)key) | (v.y ^ n)) == 0u;
-          if (!own | same) break;
-          s = (s + 1) & mask;
-          v = slots4[s];
-        }
-        if (v.w == tag) {
-          n = v.z;                              // the match goes on through entry p
-        } else {                                // the match ends before entry p: emit it and
-          D[q++] = n;                           // grow the tree by n extended with entry p
-          slots4[s] = make_uint4((uint32_t)key, n, next++, tag);
-          n = pc;
-        }
-        ++p;
-        pc = pn;
+    const uint32_t n_pairs = (uint32_t)drp[n_rows];
+    uint32_t next = (uint32_t)counts[4 * b] + 1;   // next node index (Algorithm 1's AddNode)
+    uint32_t q = 0;                                // where the next code goes
+    uint32_t p0 = 0, skip = 0;                     // segment start; entries of it already matched
+    uint32_t w0 = (uint32_t)tid < n_pairs ? Db[tid] : 0u;
+    uint32_t w1 = (uint32_t)tid + kEtBlock < n_pairs ? Db[tid + kEtBlock] : 0u;
+    barrier_global();
+    for (int64_t i = 0; i < n_rows; ++i) {
+      if (i % kEtBlock == 0) {                     // the ends of the next tuples
+        __syncthreads();
+        if (i + tid < n_rows) ends[tid] = (uint32_t)drp[i + tid + 1];
+        __syncthreads();
       }
-      D[q++] = n;                               // the last match ends the tuple
+      const uint32_t pe = ends[i % kEtBlock];
+      if (tid == 0) drp[i] = q;
+      while (p0 < pe) {                            // a segment of the tuple
+        const uint32_t j = p0 + tid;
+        const bool valid = j < pe;
+        pairs[tid] = w0;
+        pairs[tid + kEtBlock] = w1;
+        const uint32_t p1 = min(p0 + kEtBlock, pe);
+        w0 = p1 + tid < n_pairs ? Db[p1 + tid] : 0u;          // the next segment's
+        w1 = p1 + tid + kEtBlock < n_pairs ? Db[p1 + tid + kEtBlock] : 0u;
+        __syncthreads();
+        // the longest match from entry j; slot: where its key was not found
+        uint32_t n = pairs[tid], l = 1, slot = 0;
+        uint64_t key = 0;
+        bool more = valid && j + 1 < pe;
+        if (more) {
+          key = ((uint64_t)n << 32) | pairs[tid + 1];
+          slot = mix64(key) & mask;
+        }
+        while (more) {
+          const uint64_t k = load_agent64(&tab[slot].key), child = load_agent64(&tab[slot].child);
+          if (k == kEmptyKey) {
+            more = false;
+          } else if (k == key) {
+            n = (uint32_t)child;
+            ++l;
+            more = j + l < pe;
+            if (more) {
+              const uint32_t at = tid + l;
+              key = ((uint64_t)n << 32) | (at < 2 * kEtBlock ? pairs[at] : Db[j + l]);
+              slot = mix64(key) & mask;
+            }
+          } else {
+            slot = (slot + 1) & mask;
+          }
+        }
+        len[tid] = l;
+        const uint64_t mm = __ballot(valid && l > 1);
+        if (lane == 0) multi[wave] = mm;
+        __syncthreads();
+        // the greedy matches: from entry to entry while matches are one pair long, over
+        // the pairs of the longer ones
+        if (wave == 0) {
+          uint32_t at = skip;
+          const uint32_t n_seg = p1 - p0;
+          for (int w = 0; w < kEtWaves; ++w) {
+            const uint32_t wl = len[w * kEpWave + lane];
+            const uint64_t m = multi[w];
+            const uint32_t m_lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)m);
+            const uint32_t m_hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(m >> 32));
+            const uint64_t ms = ((uint64_t)m_hi << 32) | m_lo;
+            const uint32_t lo = w * kEpWave, hi = min(n_seg, lo + kEpWave);
+            uint64_t t = 0;
+            while (at < hi) {
+              const uint32_t f = at - lo;
+              const uint64_t rest = ms >> f;
+              if (rest == 0) {
+                t |= ~0ull << f;
+                at = hi;
+              } else {
+                const uint32_t z = (uint32_t)__builtin_ctzll(rest);
+                t |= ((2ull << z) - 1) << f;
+                at += z + (uint32_t)__builtin_amdgcn_readlane((int)wl, (int)(f + z));
+              }
+            }
+            if (hi < lo + kEpWave) t &= hi > lo ? (1ull << (hi - lo)) - 1 : 0ull;
+            if (lane == 0) take[w] = t;
+          }
+          if (lane == 0) after = at;
+        }
+        __syncthreads();
+        uint32_t rank = 0, total = 0;
+#pragma unroll
+        for (int w = 0; w < kEtWaves; ++w) {
+          const uint32_t c = (uint32_t)__popcll(take[w]);
+          rank += w < wave ? c : 0u;
+          total += c;
+        }
+        const uint64_t mine = take[wave];
+        if ((mine >> lane) & 1ull) {
+          rank += (uint32_t)__popcll(mine & ((1ull << lane) - 1));
+          Db[q + rank] = n;
+          if (j + l < pe) {                        // the tree grows by the match and its next pair
+            while (true) {
+              const uint64_t old = atomicCAS((unsigned long long *)&tab[slot].key,
+                                             (unsigned long long)kEmptyKey, (unsigned long long)key);
+              if (old == kEmptyKey) break;
+              slot = (slot + 1) & mask;
+            }
+            tab[slot].child = next + rank;
+          }
+        }
+        const uint32_t stop = after;
+        q += total;
+        // the match that ends the tuple adds no node
+        next += total - (total && p0 + stop == pe ? 1u : 0u);
+        skip = p1 < pe ? stop - (p1 - p0) : 0u;
+        p0 = p1;
+        barrier_global();
+      }
     }
-    drp[r1 - r0] = q - e0;
-    counts[4 * b + 1] = q - e0;
-    counts[4 * b + 2] = next;
+    if (tid == 0) {
+      drp[n_rows] = q;
+      counts[4 * b + 1] = q;
+      counts[4 * b + 2] = next;
+    }
+    __syncthreads();
   }
 }
 
@@ -370,18 +473,13 @@ toc_status toc_encode_device(int64_t n_batches, const int32_t *n_rows, int32_t n
       hipStreamSynchronize(s) != hipSuccess)
     return fail(TOC_EDEVICE, "copy of the row offsets failed");
   ChildSlot *ctab = (ChildSlot *)(w + p.off_child);
-  // tags of 0xFFFFFFFF name no batch: every child table starts empty
-  if (hipMemsetAsync(ctab, 0xFF, (size_t)(p.lanes * p.child_stride) * sizeof(ChildSlot), s) !=
-      hipSuccess)
-    return fail(TOC_EDEVICE, "clearing the child tables failed");
   hipLaunchKernelGGL(enc_pairs_kernel, dim3((unsigned)p.groups), dim3(kEpBlock), 0, s, rowptr, col,
                      val, n_cols, nnz, roff, n_batches, max_nnz, (PairSlot *)(w + p.off_pair),
                      p.pair_stride, I_col, I_val, D_codes, D_rowptr, counts, status);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(TOC_EDEVICE, "enc_pairs_kernel: %s", hipGetErrorString(e));
-  hipLaunchKernelGGL(enc_tuples_kernel, dim3((unsigned)((p.lanes + kEtBlock - 1) / kEtBlock)),
-                     dim3(kEtBlock), 0, s, rowptr, roff, n_batches, p.lanes, ctab, p.child_stride,
-                     D_codes, D_rowptr, counts, status);
+  hipLaunchKernelGGL(enc_tuples_kernel, dim3((unsigned)p.lanes), dim3(kEtBlock), 0, s, rowptr,
+                     roff, n_batches, ctab, p.child_stride, D_codes, D_rowptr, counts, status);
   e = hipGetLastError();
   if (e != hipSuccess) return fail(TOC_EDEVICE, "enc_tuples_kernel: %s", hipGetErrorString(e));
   return TOC_OK;
