@@ -227,14 +227,18 @@ __global__ __launch_bounds__(BLK) void right_k1_kernel(Img im, int64_t b0,
       if (c < n1) H[c] = fmaf(v[i], w[i], 0.0f);
     }
     __syncthreads();
+    // (the next level's bound is loaded a level ahead)
+    uint32_t a = n1, e = bt.n_levels >= 2 ? lvl[2] : 0u;
     for (int d = 2; d <= bt.n_levels; ++d) {
-      const uint32_t a = lvl[d - 1], e = lvl[d];
+      const uint32_t next = lvl[min(d + 1, bt.n_levels)];
 #pragma unroll
       for (int i = 0; i < kK1RegCodes; ++i) {
         const uint32_t c = threadIdx.x + (uint32_t)(i * BLK);
         if (c >= a && c < e) H[c] = fmaf(v[i], w[i], H[pr[i]]);
       }
       __syncthreads();
+      a = e;
+      e = next;
     }
   } else {
     for (int d = 1; d <= bt.n_levels; ++d) {
@@ -315,14 +319,17 @@ __device__ inline OccIndex occ_index(const Img &im, const uint32_t *occ_off_all,
   return x;
 }
 
-template <int NCOL>
-__global__ __launch_bounds__(kBlock) void left_k1_kernel(
+// BLK threads; SPLIT: a batch's columns dealt to `parts` workgroups (else parts is 1).
+template <int NCOL, int BLK, bool SPLIT>
+__global__ __launch_bounds__(BLK) void left_k1_kernel(
     Img im, const uint32_t *__restrict__ occ_off_all, const uint32_t *__restrict__ tlist_all,
     const uint32_t *__restrict__ cols_all, const uint32_t *__restrict__ tchild_all, int64_t b0,
-    int32_t m, int32_t max_rows, int32_t max_codes, const float *__restrict__ G, int64_t ldg,
+    int32_t m, int32_t max_rows, int32_t max_codes, int32_t parts,
+    const float *__restrict__ G, int64_t ldg,
     float *__restrict__ out, int64_t ldo, int accumulate) {
   extern __shared__ float sm[];
-  const int64_t b = b0 + blockIdx.x;
+  const int64_t b = b0 + (SPLIT ? blockIdx.x / parts : blockIdx.x);
+  const int part = SPLIT ? (int)(blockIdx.x % parts) : 0;
   const toc_batch bt = uniform_batch(im.batches + b);
   const uint32_t *lvl = im.level + bt.lvl_base;
   const OccIndex ox = occ_index(im, occ_off_all, bt, b);
@@ -332,6 +339,18 @@ __global__ __launch_bounds__(kBlock) void left_k1_kernel(
   const uint32_t nc = (uint32_t)bt.n_codes, ni = (uint32_t)bt.n_int1;
   float *Gs = sm;                                     // max_rows
   float *H = sm + max_rows;                           // max_codes
+  // the part's columns, whose leaves are one stretch of positions, and every tree
+  // code: x counts the positions this workgroup sums
+  const uint32_t *Loff = cx, *Toff = cx + 2 * (m + 1);
+  const int width = (m + parts - 1) / parts;
+  const int jb = SPLIT ? min(m, part * width) : 0, je = SPLIT ? min(m, jb + width) : m;
+  const uint32_t la = SPLIT ? (uint32_t)__builtin_amdgcn_readfirstlane((int)Loff[jb]) : ni;
+  const uint32_t lb = SPLIT ? (uint32_t)__builtin_amdgcn_readfirstlane((int)Loff[je]) : ox.n1;
+  const uint32_t nx = SPLIT ? ni + (lb - la) + (nc - ox.n1) : nc;
+  auto position = [&](uint32_t x) -> uint32_t {
+    if (!SPLIT) return x;
+    return x < ni ? x : x < ni + (lb - la) ? la + (x - ni) : ox.n1 + (x - ni - (lb - la));
+  };
   auto hrow = [&](uint32_t c) -> uint32_t { return ox.hrow(c); };
   float *ob = out + b * (int64_t)m * ldo;
   // G(c) for every code; a leaf's times its value (read beside its first
@@ -342,23 +361,23 @@ __global__ __launch_bounds__(kBlock) void left_k1_kernel(
   auto load_pass = [&](uint32_t c0) {
 #pragma unroll
     for (int u = 0; u < kK1Codes; ++u) {
-      const uint32_t c = c0 + u * kBlock;
-      o0[u] = c < nc ? ox.start(c) : 0u;
-      o1[u] = c < nc ? ox.end(c) : 0u;
+      const uint32_t x = c0 + u * BLK, c = position(x);
+      o0[u] = x < nx ? ox.start(c) : 0u;
+      o1[u] = x < nx ? ox.end(c) : 0u;
     }
 #pragma unroll
     for (int u = 0; u < kK1Codes; ++u) {
-      const uint32_t c = c0 + u * kBlock;
+      const uint32_t x = c0 + u * BLK, c = position(x);
       // 1.0 for a tree code; a leaf without occurrences (kept dead code) sums to 0
-      vb[u] = c < nc && ox.leaf(c) && o1[u] > o0[u] ? ox.cv[o0[u]] : 0x3F800000u;
+      vb[u] = x < nx && ox.leaf(c) && o1[u] > o0[u] ? ox.cv[o0[u]] : 0x3F800000u;
 #pragma unroll
       for (int v = 0; v < kK1Occ; ++v) w[u][v] = o0[u] + v < o1[u] ? ox.ce[o0[u] + v] : 0xFFFFFFFFu;
     }
   };
   load_pass(threadIdx.x);
-  for (int r = threadIdx.x; r < bt.n_rows; r += kBlock) Gs[r] = G[(bt.row_base + r) * ldg];
+  for (int r = threadIdx.x; r < bt.n_rows; r += BLK) Gs[r] = G[(bt.row_base + r) * ldg];
   __syncthreads();
-  for (uint32_t c0 = threadIdx.x; c0 < nc; c0 += kBlock * kK1Codes) {
+  for (uint32_t c0 = threadIdx.x; c0 < nx; c0 += BLK * kK1Codes) {
     if (c0 != threadIdx.x) load_pass(c0);
     float s[kK1Codes];
 #pragma unroll
@@ -373,34 +392,57 @@ __global__ __launch_bounds__(kBlock) void left_k1_kernel(
     }
 #pragma unroll
     for (int u = 0; u < kK1Codes; ++u) {
-      const uint32_t c = c0 + u * kBlock;
-      if (c < nc) H[c] = ox.leaf(c) ? __uint_as_float(vb[u]) * s[u] : s[u];
+      const uint32_t x = c0 + u * BLK, c = position(x);
+      if (x < nx) H[c] = ox.leaf(c) ? __uint_as_float(vb[u]) * s[u] : s[u];
     }
   }
   __syncthreads();
   // children into parents, deepest parent level first
-  for (int d = bt.n_levels - 1; d >= 1; --d) {
-    const uint32_t a = d == 1 ? 0 : lvl[d - 1], e = d == 1 ? ni : lvl[d];
-    for (uint32_t c = a + threadIdx.x; c < e; c += kBlock) {
-      const uint32_t h = hrow(c);
-      H[c] += blocked_sum(tch[h], tch[h + 1], 1u, [&](uint32_t ch) { return ch; },
-                          [&](uint32_t ch) { return H[ch]; });
+  // (each thread's first code of a level, and its children, are loaded a level ahead,
+  // as is the level's bound: a level then waits for LDS only)
+  {
+    auto bound = [&](int d) -> uint32_t { return d <= 1 ? 0u : lvl[d - 1]; };
+    int d = bt.n_levels - 1;
+    uint32_t e = d > 1 ? lvl[d] : ni, a = bound(d), below = bound(d - 1);
+    uint32_t ch0 = 0, ch1 = 0;
+    auto children = [&](uint32_t c, uint32_t end) {
+      const uint32_t h = hrow(c < end ? c : 0u);
+      ch0 = c < end ? tch[h] : 0u;
+      ch1 = c < end ? tch[h + 1] : 0u;
+    };
+    if (d >= 1) children(a + threadIdx.x, e);
+    for (; d >= 1; --d) {
+      const uint32_t c0 = ch0, c1 = ch1;
+      const uint32_t next_e = d - 1 == 1 ? ni : a, next_a = below;
+      if (d > 1) children(next_a + threadIdx.x, next_e);
+      below = bound(d - 2);
+      const uint32_t c = a + threadIdx.x;
+      if (c < e)
+        H[c] += blocked_sum(c0, c1, 1u, [&](uint32_t ch) { return ch; },
+                            [&](uint32_t ch) { return H[ch]; });
+      for (uint32_t c = a + threadIdx.x + BLK; c < e; c += BLK) {
+        const uint32_t h = hrow(c);
+        H[c] += blocked_sum(tch[h], tch[h + 1], 1u, [&](uint32_t ch) { return ch; },
+                            [&](uint32_t ch) { return H[ch]; });
+      }
+      __syncthreads();
+      e = next_e;
+      a = next_a;
     }
-    __syncthreads();
   }
   // a tree code's H becomes val * H (the leaves' already are): a key column's
   // output is the plain sum of these over the column's codes
   const uint32_t n_tree = ni + (nc - ox.n1);
-  for (uint32_t t0 = threadIdx.x; t0 < n_tree; t0 += kBlock * kK1Codes) {
+  for (uint32_t t0 = threadIdx.x; t0 < n_tree; t0 += BLK * kK1Codes) {
     float v[kK1Codes];
 #pragma unroll
     for (int u = 0; u < kK1Codes; ++u) {
-      const uint32_t t = t0 + u * kBlock, c = t < ni ? t : t - ni + ox.n1;
+      const uint32_t t = t0 + u * BLK, c = t < ni ? t : t - ni + ox.n1;
       v[u] = t < n_tree ? ox.key[c].val : 0.0f;
     }
 #pragma unroll
     for (int u = 0; u < kK1Codes; ++u) {
-      const uint32_t t = t0 + u * kBlock, c = t < ni ? t : t - ni + ox.n1;
+      const uint32_t t = t0 + u * BLK, c = t < ni ? t : t - ni + ox.n1;
       if (t < n_tree) H[c] *= v[u];
     }
   }
@@ -408,13 +450,12 @@ __global__ __launch_bounds__(kBlock) void left_k1_kernel(
   // each key column once: its depth-1 leaves (a code range), then its tree
   // codes (a tree-list range); a thread has NCOL columns in flight and
   // loads the first kK1Tree tree-list entries of each before summing
-  const uint32_t *Loff = cx, *Toff = cx + 2 * (m + 1);
-  for (int j0 = 0; j0 < m; j0 += kBlock * NCOL) {
+  for (int j0 = jb; j0 < je; j0 += BLK * NCOL) {
     uint32_t l0[NCOL], l1[NCOL], t0[NCOL], t1[NCOL];
 #pragma unroll
     for (int u = 0; u < NCOL; ++u) {
-      const int j = j0 + u * kBlock + threadIdx.x;
-      const bool in = j < m;
+      const int j = j0 + u * BLK + threadIdx.x;
+      const bool in = j < je;
       l0[u] = in ? Loff[j] : 0u;
       l1[u] = in ? Loff[j + 1] : 0u;
       t0[u] = in ? Toff[j] : 0u;
@@ -427,7 +468,7 @@ __global__ __launch_bounds__(kBlock) void left_k1_kernel(
       for (int v = 0; v < kK1Tree; ++v) tc[u][v] = t0[u] + v < t1[u] ? tl[t0[u] + v] : 0xFFFFFFFFu;
 #pragma unroll
     for (int u = 0; u < NCOL; ++u) {
-      const int j = j0 + u * kBlock + threadIdx.x;
+      const int j = j0 + u * BLK + threadIdx.x;
       float sum = blocked_sum(l0[u], l1[u], 1u, [&](uint32_t c) { return c; },
                               [&](uint32_t c) { return H[c]; });
       float tsum = 0.0f;
@@ -438,7 +479,7 @@ __global__ __launch_bounds__(kBlock) void left_k1_kernel(
       if (t1[u] > t0[u] + kK1Tree)
         sum += blocked_sum(t0[u] + kK1Tree, t1[u], 1u, [&](uint32_t t) { return tl[t]; },
                            [&](uint32_t c) { return H[c]; });
-      if (j < m) {
+      if (j < je) {
         float *p = ob + (int64_t)j * ldo;
         *p = accumulate ? *p + sum : sum;
       }
@@ -3239,12 +3280,17 @@ toc_status toc_right_mul(const toc_dev *d, const float *W, int32_t k, int64_t ld
     const int lpr = lanes_per_row(d);
     for (int64_t b0 = 0; b0 < nb; b0 += (1 << 30)) {
       const unsigned g = (unsigned)std::min<int64_t>(nb - b0, 1 << 30);
+      // (few batches: a CU's waves for each)
       switch (lpr) {
+#define TOC_RK1_BLK(L, BLK)                                                                \
+  do {                                                                                     \
+    if ((st = allow_lds(right_k1_kernel<L, BLK>, lds))) return st;                         \
+    hipLaunchKernelGGL((right_k1_kernel<L, BLK>), dim3(g), dim3(BLK), lds, s, im, b0, W, ldw, R, ldr); \
+  } while (0)
 #define TOC_RK1(L)                                                                         \
   case L:                                                                                  \
-    if ((st = allow_lds(right_k1_kernel<L, kK1RightBlock>, lds))) return st;               \
-    hipLaunchKernelGGL((right_k1_kernel<L, kK1RightBlock>), dim3(g), dim3(kK1RightBlock), lds, s, \
-                       im, b0, W, ldw, R, ldr);                                            \
+    if (nb <= 256) TOC_RK1_BLK(L, 1024);                                                   \
+    else TOC_RK1_BLK(L, kK1RightBlock);                                                    \
     break;
         TOC_RK1(4)
         TOC_RK1(8)
@@ -3252,6 +3298,7 @@ toc_status toc_right_mul(const toc_dev *d, const float *W, int32_t k, int64_t ld
         TOC_RK1(32)
         default: TOC_RK1(64)
 #undef TOC_RK1
+#undef TOC_RK1_BLK
       }
       if ((st = launch_status("right_k1_kernel"))) return st;
     }
@@ -3330,20 +3377,37 @@ toc_status left_mul_impl(const toc_dev *d, const float *G, int32_t k, int64_t ld
   if (k == 1 && k1_fits(d, TOC_OP_LEFT)) {
     const size_t lds = k1_lds(d, TOC_OP_LEFT);
     const bool wide_m = m > 4 * kBlock;      // a pass of 4 columns per thread covers 4 kBlock
-    if ((st = allow_lds(wide_m ? left_k1_kernel<8> : left_k1_kernel<4>, lds))) return st;
+    // Few batches leave most CUs idle with a workgroup each: then a batch's columns are
+    // dealt to several, which each sum every tree code and the leaves of their own
+    // columns.  That pays where most codes are leaves (the tree codes' part is done by
+    // each) and a part still has columns for its threads.
+    // 300 sparse text batches (47,236 columns): 256 -> 161 us with 6 parts (as many
+    // workgroups as the LDS lets run at once; half or twice that many are slower).
+    const int64_t parts = d->max_tree * 8 > d->max_codes
+                              ? 1
+                              : std::max<int64_t>(1, std::min<int64_t>({(1536 + nb - 1) / nb, 8, m / kBlock}));
+    // a CU to itself: all its waves for one batch
+    const bool alone = nb * parts <= 256;
     const uint8_t *bb = (const uint8_t *)d->buf;
     const uint32_t *occ_off = (const uint32_t *)(bb + d->layout.occ_off);
     const uint32_t *tlist = (const uint32_t *)(bb + d->layout.tlist);
     const uint32_t *cols = (const uint32_t *)(bb + d->layout.cols);
     const uint32_t *tchild = (const uint32_t *)(bb + d->layout.tchild);
-    for (int64_t b0 = 0; b0 < nb; b0 += (1 << 30)) {
-      const unsigned g = (unsigned)std::min<int64_t>(nb - b0, 1 << 30);
-      if (wide_m)
-        hipLaunchKernelGGL(left_k1_kernel<8>, dim3(g), dim3(kBlock), lds, s, im, occ_off, tlist, cols,
-                           tchild, b0, m, d->max_rows, d->max_codes, G, ldg, out, ldo, accumulate);
-      else
-        hipLaunchKernelGGL(left_k1_kernel<4>, dim3(g), dim3(kBlock), lds, s, im, occ_off, tlist, cols,
-                           tchild, b0, m, d->max_rows, d->max_codes, G, ldg, out, ldo, accumulate);
+    for (int64_t b0 = 0; b0 < nb; b0 += (1 << 22)) {
+      const unsigned g = (unsigned)(std::min<int64_t>(nb - b0, 1 << 22) * parts);
+#define TOC_LK1(NCOL, BLK, SPLIT)                                                                \
+  do {                                                                                          \
+    if ((st = allow_lds(left_k1_kernel<NCOL, BLK, SPLIT>, lds))) return st;                     \
+    hipLaunchKernelGGL((left_k1_kernel<NCOL, BLK, SPLIT>), dim3(g), dim3(BLK), lds, s, im, occ_off,  \
+                       tlist, cols, tchild, b0, m, d->max_rows, d->max_codes, (int)parts, G, ldg,   \
+                       out, ldo, accumulate);                                                   \
+  } while (0)
+      if (alone && parts > 1) TOC_LK1(4, 1024, true);
+      else if (alone) TOC_LK1(4, 1024, false);
+      else if (parts > 1) TOC_LK1(8, kBlock, true);
+      else if (wide_m) TOC_LK1(8, kBlock, false);
+      else TOC_LK1(4, kBlock, false);
+#undef TOC_LK1
       if ((st = launch_status("left_k1_kernel"))) return st;
     }
     return TOC_OK;
