@@ -24,7 +24,9 @@ namespace {
 
 constexpr int kNnBlock = 1024;
 constexpr int kNnLanes = 16;                 // lanes per tuple in the forward product
-constexpr int kNnCodes = 8;                  // a lane's codes whose loads fly together there
+constexpr int kNnCodes = 8;                  // a lane's codes whose rows' loads fly together there
+constexpr int kNnAhead = 16;                 // a lane's codes whose keys are loaded ahead
+constexpr uint32_t kNnNone = 0xFFFFFFFFu;
 constexpr uint32_t kNnFirst = 0x80000000u;   // first-occurrence bit of a leaf occurrence
 constexpr size_t kNnLdsMax = 160 * 1024;
 constexpr int kColGroups = 8;                // workgroups sharing a slice's key columns
@@ -74,6 +76,27 @@ __global__ __launch_bounds__(kNnBlock) void mlp_fwd1_kernel(NnImg im, int64_t b,
   const toc_key *key = im.key + bt.code_base;
   const toc_link *link = im.link + (bt.deep_base - (int64_t)bt.n_lvl1);   // depth >= 2 only
   auto wrow = [&](uint32_t col) { return *(const float4 *)(W1 + (int64_t)col * h1 + u0); };
+  const uint32_t *span = im.span + bt.span_base;
+  const uint32_t *dc = im.dcodes + bt.d_base;
+  const int lane = threadIdx.x % kNnLanes, grp = threadIdx.x / kNnLanes;
+  const float4 bias = *(const float4 *)(b1 + u0);
+  const int r = blockIdx.y * (kNnBlock / kNnLanes) + grp;
+  const uint32_t s = r < bt.n_rows ? span[r] : 0u, e = r < bt.n_rows ? span[r + 1] : 0u;
+  // the lane's first kNnAhead codes and their keys are loaded before the table's levels,
+  // which do not need them; then kNnCodes rows at a time are loaded together, and
+  // summed in order
+  uint32_t c[kNnAhead];
+  toc_key k[kNnAhead];
+  auto load_codes = [&](uint32_t j0) {
+#pragma unroll
+    for (int q = 0; q < kNnAhead; ++q) {
+      const uint32_t j = j0 + (uint32_t)(q * kNnLanes);
+      c[q] = j < e ? dc[j] : kNnNone;
+    }
+#pragma unroll
+    for (int q = 0; q < kNnAhead; ++q) k[q] = c[q] < n1 ? key[c[q]] : toc_key{0u, 0.0f};
+  };
+  load_codes(s + lane);
   for (int d = 2; d <= bt.n_levels; ++d) {
     const uint32_t a = lvl[d - 1], e = lvl[d];
     for (uint32_t c = a + threadIdx.x; c < e; c += kNnBlock) {
@@ -90,37 +113,24 @@ __global__ __launch_bounds__(kNnBlock) void mlp_fwd1_kernel(NnImg im, int64_t b,
     }
     rows_barrier<kGlobal>();
   }
-  const uint32_t *span = im.span + bt.span_base;
-  const uint32_t *dc = im.dcodes + bt.d_base;
-  const int lane = threadIdx.x % kNnLanes, grp = threadIdx.x / kNnLanes;
-  const float4 bias = *(const float4 *)(b1 + u0);
-  const int r = blockIdx.y * (kNnBlock / kNnLanes) + grp;
   if (r < bt.n_rows) {
-    const uint32_t s = span[r], e = span[r + 1];
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    // kNnCodes of the lane's codes at a time: their codes, then their keys, then
-    // their rows are loaded together, and summed in order
-    for (uint32_t j0 = s + lane; j0 < e; j0 += kNnLanes * kNnCodes) {
-      uint32_t c[kNnCodes];
-      toc_key k[kNnCodes];
-      float4 w[kNnCodes];
+    for (uint32_t j0 = s + lane; j0 < e; j0 += kNnLanes * kNnAhead) {
+      if (j0 != s + lane) load_codes(j0);
 #pragma unroll
-      for (int q = 0; q < kNnCodes; ++q) {
-        const uint32_t j = j0 + (uint32_t)(q * kNnLanes);
-        c[q] = j < e ? dc[j] : 0xFFFFFFFFu;
-      }
+      for (int h = 0; h < kNnAhead; h += kNnCodes) {
+        float4 w[kNnCodes];
 #pragma unroll
-      for (int q = 0; q < kNnCodes; ++q) k[q] = c[q] < n1 ? key[c[q]] : toc_key{0u, 0.0f};
+        for (int q = 0; q < kNnCodes; ++q) {
+          w[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (c[h + q] < n1) w[q] = wrow(k[h + q].col);
+          else if (c[h + q] != kNnNone) w[q] = Hd[c[h + q] - n1];
+        }
 #pragma unroll
-      for (int q = 0; q < kNnCodes; ++q) {
-        w[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (c[q] < n1) w[q] = wrow(k[q].col);
-        else if (c[q] != 0xFFFFFFFFu) w[q] = Hd[c[q] - n1];
-      }
-#pragma unroll
-      for (int q = 0; q < kNnCodes; ++q) {
-        if (c[q] < n1) acc = fma4(k[q].val, w[q], acc);
-        else if (c[q] != 0xFFFFFFFFu) acc = add4(acc, w[q]);
+        for (int q = 0; q < kNnCodes; ++q) {
+          if (c[h + q] < n1) acc = fma4(k[h + q].val, w[q], acc);
+          else if (c[h + q] != kNnNone) acc = add4(acc, w[q]);
+        }
       }
     }
 #pragma unroll
@@ -182,14 +192,20 @@ __global__ __launch_bounds__(kNnBlock) void mlp_rows_kernel(
     stage<kNnBlock>(W3s, h2 * C, [&](int x) { return W3g[x]; });
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < nr * h2; idx += kNnBlock) {
+  // (four lanes to a unit, each a quarter of the sum)
+  for (int x = threadIdx.x; x < 4 * nr * h2; x += kNnBlock) {
+    const int idx = x / 4, part = x % 4;
     const int i = idx / h2, u = idx - i * h2;
     const float *a = A + i * h1;
-    float z = b2[u];
-    for (int v = 0; v < h1; ++v) z = fmaf(a[v], W2[v * h2 + u], z);
-    const float hv = sigm(z);
-    H[idx] = hv;
-    H2g[(int64_t)i0 * h2 + idx] = hv;
+    float z = 0.0f;
+    for (int v = part; v < h1; v += 4) z = fmaf(a[v], W2[v * h2 + u], z);
+    z += __shfl_xor(z, 1, 4);
+    z += __shfl_xor(z, 2, 4);
+    if (part == 0) {
+      const float hv = sigm(z + b2[u]);
+      H[idx] = hv;
+      H2g[(int64_t)i0 * h2 + idx] = hv;
+    }
   }
   __syncthreads();
   for (int idx = threadIdx.x; idx < nr * C; idx += kNnBlock) {
@@ -249,36 +265,60 @@ __global__ __launch_bounds__(kNnBlock) void mlp_rows_kernel(
 // step stages its inputs with one load latency.  Runs after every tuple's dZ1 was
 // computed from the old W2.
 
-__global__ __launch_bounds__(256) void mlp_grad_kernel(
+//
+// Four quarters of 256 threads share a block's entries, each over a quarter of the
+// tuples, and add up in LDS: a 250-tuple step is bound by the latency of staging and of
+// the serial sums, both a quarter as long (18.4 -> 10.6 us with 256 threads' work on
+// 784-200-50-10 image batches).
+constexpr int kGradParts = 4;
+__global__ __launch_bounds__(256 * kGradParts) void mlp_grad_kernel(
     int n, int n_w2, const float *__restrict__ act1, int h1, int h2, int C,
     const float *__restrict__ H2g, const float *__restrict__ dZ2g, const float *__restrict__ dZ3g,
     float lr, float *__restrict__ W2, float *__restrict__ b2, float *__restrict__ W3,
     float *__restrict__ b3, int ch2, int ch3) {
   extern __shared__ float gs[];
+  __shared__ float part_g[kGradParts][256], part_b[kGradParts][256];
+  constexpr int NT = 256 * kGradParts;
+  const int tid = threadIdx.x % 256, part = threadIdx.x / 256;
+  // the sum of the quarters' g (and gb), valid in the first
+  auto add_parts = [&](float &g, float &gb) {
+    part_g[part][tid] = g;
+    part_b[part][tid] = gb;
+    __syncthreads();
+    if (part == 0)
+#pragma unroll
+      for (int p = 1; p < kGradParts; ++p) {
+        g += part_g[p][tid];
+        gb += part_b[p][tid];
+      }
+  };
   if ((int)blockIdx.x < n_w2) {
     const int U = min(h2, 256), V = 256 / U, nub = (h2 + U - 1) / U;
     const int v0 = (blockIdx.x / nub) * V, u0 = (blockIdx.x % nub) * U;
     float *As = gs, *Gs = gs + ch2 * V;
-    const int lv = threadIdx.x / U, lu = threadIdx.x - lv * U;
+    const int lv = tid / U, lu = tid - lv * U;
     const int v = v0 + lv, u = u0 + lu;
     float g = 0.0f, gb = 0.0f;                  // gb: b2's gradient, by the first row of blocks
     for (int i0 = 0; i0 < n; i0 += ch2) {
       const int ni = min(ch2, n - i0);
-      stage<256>(As, ni * V, [&](int x) {
+      stage<NT>(As, ni * V, [&](int x) {
         const int ii = x / V, vv = v0 + (x - ii * V);
         return vv < h1 ? act1[(int64_t)(i0 + ii) * h1 + vv] : 0.0f;
       });
-      stage<256>(Gs, ni * U, [&](int x) {
+      stage<NT>(Gs, ni * U, [&](int x) {
         const int ii = x / U, uu = u0 + (x - ii * U);
         return uu < h2 ? dZ2g[(int64_t)(i0 + ii) * h2 + uu] : 0.0f;
       });
       __syncthreads();
+      const int ia = ni * part / kGradParts, ie = ni * (part + 1) / kGradParts;
       if (lv < V)
-        for (int ii = 0; ii < ni; ++ii) g = fmaf(As[ii * V + lv], Gs[ii * U + lu], g);
+        for (int ii = ia; ii < ie; ++ii) g = fmaf(As[ii * V + lv], Gs[ii * U + lu], g);
       if (v0 == 0 && lv == 0)
-        for (int ii = 0; ii < ni; ++ii) gb += Gs[ii * U + lu];
+        for (int ii = ia; ii < ie; ++ii) gb += Gs[ii * U + lu];
       __syncthreads();
     }
+    add_parts(g, gb);
+    if (part != 0) return;
     if (lv < V && v < h1 && u < h2) W2[v * h2 + u] = fmaf(-lr, g, W2[v * h2 + u]);
     if (v0 == 0 && lv == 0 && u < h2) b2[u] = fmaf(-lr, gb, b2[u]);
     return;
@@ -287,21 +327,22 @@ __global__ __launch_bounds__(256) void mlp_grad_kernel(
   const int TI = ch3;
   float *Hs = gs, *Zs = gs + TI * h2;
   const int n_out3 = (h2 + 1) * C;
-  {
-    const int idx = ((int)blockIdx.x - n_w2) * 256 + threadIdx.x, u = idx / C, c = idx - u * C;
-    float g = 0.0f;
-    for (int i0 = 0; i0 < n; i0 += TI) {
-      const int ni = min(TI, n - i0);
-      stage<256>(Hs, ni * h2, [&](int x) { return H2g[(int64_t)i0 * h2 + x]; });
-      stage<256>(Zs, ni * C, [&](int x) { return dZ3g[(int64_t)i0 * C + x]; });
-      __syncthreads();
-      if (idx < n_out3)
-        for (int ii = 0; ii < ni; ++ii) g = fmaf(u < h2 ? Hs[ii * h2 + u] : 1.0f, Zs[ii * C + c], g);
-      __syncthreads();
-    }
-    if (idx < h2 * C) W3[idx] = fmaf(-lr, g, W3[idx]);
-    else if (idx < n_out3) b3[c] = fmaf(-lr, g, b3[c]);
+  const int idx = ((int)blockIdx.x - n_w2) * 256 + tid, u = idx / C, c = idx - u * C;
+  float g = 0.0f, none = 0.0f;
+  for (int i0 = 0; i0 < n; i0 += TI) {
+    const int ni = min(TI, n - i0);
+    stage<NT>(Hs, ni * h2, [&](int x) { return H2g[(int64_t)i0 * h2 + x]; });
+    stage<NT>(Zs, ni * C, [&](int x) { return dZ3g[(int64_t)i0 * C + x]; });
+    __syncthreads();
+    const int ia = ni * part / kGradParts, ie = ni * (part + 1) / kGradParts;
+    if (idx < n_out3)
+      for (int ii = ia; ii < ie; ++ii) g = fmaf(u < h2 ? Hs[ii * h2 + u] : 1.0f, Zs[ii * C + c], g);
+    __syncthreads();
   }
+  add_parts(g, none);
+  if (part != 0) return;
+  if (idx < h2 * C) W3[idx] = fmaf(-lr, g, W3[idx]);
+  else if (idx < n_out3) b3[c] = fmaf(-lr, g, b3[c]);
 }
 
 // Weight gradient of the first layer for hidden units u0 .. u0+3, by pulling:
@@ -468,10 +509,12 @@ int64_t row_groups_max(const toc_dev *d) {
   return std::max<int64_t>(1, (d->max_rows + kNnBlock / kNnLanes - 1) / (kNnBlock / kNnLanes));
 }
 
-// Tuples per workgroup of mlp_rows_kernel: up to 8, as many as fit 40 KiB of LDS.
+// Tuples per workgroup of mlp_rows_kernel: up to 4 (a batch of 250 then keeps 63 CUs
+// busy; with 8 tuples and a thread to a unit the kernel took 14.7 us, now 11.4),
+// as many as fit 40 KiB of LDS.
 int rows_per_group(int h1, int h2, int C) {
   const int per = h1 + 2 * h2 + C;
-  return std::max(1, std::min(8, (40 * 1024 / 4) / per));
+  return std::max(1, std::min(4, (40 * 1024 / 4) / per));
 }
 
 // Most deep codes and most tree codes (depth-1 codes with children plus deep
@@ -601,7 +644,8 @@ toc_status toc_mlp_epoch(const toc_dev *d, int64_t b0, int64_t n_batches, int32_
       hipLaunchKernelGGL(mlp_rows_kernel<false>, dim3((unsigned)((bt.n_rows + R - 1) / R)),
                          dim3(kNnBlock), lds_r, s, bt.n_rows, R, bt.row_base, act1, h1, h2, n_out,
                          W2, b2, W3, b3, labels, H2g, dZ2g, dZ3g, dz1);
-    hipLaunchKernelGGL(mlp_grad_kernel, dim3((unsigned)(n_w2 + n_w3)), dim3(256), lds_g, s, bt.n_rows, n_w2,
+    hipLaunchKernelGGL(mlp_grad_kernel, dim3((unsigned)(n_w2 + n_w3)), dim3(256 * kGradParts), lds_g, s,
+                       bt.n_rows, n_w2,
                        act1, h1, h2, n_out, H2g, dZ2g, dZ3g, lr, W2, b2, W3, b3, ch2, ch3);
     // the next step's batch with rows (its arrays are read ahead by the last
     // kernel of this step)
