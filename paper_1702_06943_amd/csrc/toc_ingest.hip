@@ -26,7 +26,10 @@ using toc::fail;
 
 constexpr int kIgBlock = kCpBlock;          // the scan helper's workgroup size
 constexpr int kIgWaves = kCpWaves;
-constexpr int kIgGrid = 512;                // persistent workgroups, one scratch slot each
+constexpr int kIgGrid = 512;                // persistent workgroups that a workspace is sized for,
+                                            // one scratch slot each
+constexpr int kIgGridMost = 1024;           // (four to a CU) that run when their slots fit in it
+constexpr uint32_t kRankMost = 512;         // largest group of D's entries ordered by ranks
 constexpr uint32_t kLive = 1u, kHasChild = 2u;
 constexpr int kCensus = 8;                  // int64 counts per batch from the census
 
@@ -83,6 +86,33 @@ __device__ void mark_live(const uint8_t *p_d, uint32_t w_d, uint32_t n_d, uint32
   __syncthreads();
   for (uint32_t c = 1 + threadIdx.x; c < n_nodes; c += kIgBlock)
     if ((flags[c] & kLive) && par[c] != 0u) atomicOr(&flags[par[c]], kHasChild);
+  __syncthreads();
+}
+
+// Words of LDS that hold a live and a has-child bit for each of n nodes.
+__host__ __device__ inline uint32_t bit_words(uint32_t n) { return 2u * ((n + 31u) / 32u); }
+
+// The same with the bits in LDS while they are found (with a global atomic per entry of D
+// and node the census of 1000 one-hot batches took 0.58 ms, now 0.23), `bits` of
+// bit_words(n_nodes) words.
+__device__ void mark_live_lds(const uint8_t *p_d, uint32_t w_d, uint32_t n_d, uint32_t n_nodes,
+                              const uint32_t *par, uint32_t *flags, uint32_t *bits) {
+  uint32_t *child = bits + (n_nodes + 31u) / 32u;
+  for (uint32_t x = threadIdx.x; x < bit_words(n_nodes); x += kIgBlock) bits[x] = 0u;
+  __syncthreads();
+  for (uint32_t p = threadIdx.x; p < n_d; p += kIgBlock) {
+    uint32_t c = rd(p_d, p, w_d);
+    while (c != 0u && (atomicOr(&bits[c / 32u], 1u << (c % 32u)) >> (c % 32u) & 1u) == 0u) c = par[c];
+  }
+  __syncthreads();
+  for (uint32_t c = 1 + threadIdx.x; c < n_nodes; c += kIgBlock) {
+    const uint32_t q = par[c];
+    if ((bits[c / 32u] >> (c % 32u) & 1u) && q != 0u) atomicOr(&child[q / 32u], 1u << (q % 32u));
+  }
+  __syncthreads();
+  for (uint32_t c = threadIdx.x; c < n_nodes; c += kIgBlock)
+    flags[c] = ((bits[c / 32u] >> (c % 32u) & 1u) ? kLive : 0u) |
+               ((child[c / 32u] >> (c % 32u) & 1u) ? kHasChild : 0u);
   __syncthreads();
 }
 
@@ -152,7 +182,8 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
     uint32_t n_cols, const int32_t *__restrict__ cp_status, const uint32_t *__restrict__ parent,
     const uint32_t *__restrict__ col, const uint32_t *__restrict__ depth,
     uint32_t *__restrict__ flags_all, uint32_t *__restrict__ colbits_all,
-    int64_t *__restrict__ counts, int32_t *__restrict__ status) {
+    int64_t *__restrict__ counts, int32_t *__restrict__ status, uint32_t lds_words) {
+  extern __shared__ uint32_t node_bits[];
   __shared__ Hdr h;
   __shared__ unsigned long long s_nnz;
   __shared__ uint32_t s_live, s_top, s_int1, s_deep, s_lvl1, s_ucols;
@@ -183,7 +214,8 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
     const uint8_t *p_d = blob + h.data[3];
     const uint32_t *par = parent + no, *cl = col + no, *dep = depth + no;
     uint32_t *fl = flags_all + no;
-    mark_live(p_d, w_d, n_d, n_nodes, par, fl);
+    if (bit_words(n_nodes) <= lds_words) mark_live_lds(p_d, w_d, n_d, n_nodes, par, fl, node_bits);
+    else mark_live(p_d, w_d, n_d, n_nodes, par, fl);
     for (uint32_t x = threadIdx.x; x < ncw; x += kIgBlock) colbits[x] = 0u;
     __syncthreads();
     uint32_t live = 0, top = 0, int1 = 0, deep = 0, lvl1 = 0;
@@ -249,6 +281,7 @@ struct IgParams {
   uint32_t *g;                  // live children before each entry of occ (+1 per batch)
   uint32_t *sortbuf;            // 4 sort_len words per workgroup
   int64_t sort_len;
+  uint32_t lds_words;           // LDS words for a batch's node bits or counts
   uint8_t *img;
   toc_layout L;
   int32_t *status;
@@ -263,13 +296,15 @@ struct IgParams {
 
 // The image arrays of each batch of the range (see toc_dev_layout_get for their
 // meaning), at the offsets of the batch table the host wrote into the image.
-__global__ __launch_bounds__(kIgBlock) void image_kernel(IgParams P) {
+// (64 registers, some of them spilled, so that four workgroups share a CU: its phases
+// wait for memory; 1000 one-hot batches 3.5 -> 2.7 ms for the whole ingest)
+__global__ __launch_bounds__(kIgBlock, 8) void image_kernel(IgParams P) {
   extern __shared__ uint32_t sm[];              // tuple starts, then nonempty tuples before each
   __shared__ Hdr h;
   __shared__ uint32_t wsum[kIgWaves];
   __shared__ uint32_t run[256], wcnt[kIgWaves * 256];
   __shared__ uint32_t s_live, s_int1, s_top, s_max;
-  uint32_t *st = sm, *nes = sm + (P.max_rows + 1);
+  uint32_t *st = sm, *nes = sm + (P.max_rows + 1), *nodes = nes + (P.max_rows + 1);
   const int64_t n = P.n;
   const int64_t *node_off = P.offs + (n + 1), *d_off = P.offs + 2 * (n + 1),
                 *dt_off = P.offs + 3 * (n + 1);
@@ -319,11 +354,17 @@ __global__ __launch_bounds__(kIgBlock) void image_kernel(IgParams P) {
         const uint32_t v = scan_step(r < n_r && st[r + 1] > st[r] ? 1u : 0u, wsum, carry);
         if (r < n_r) nes[r] = v;
       }
-      mark_live(p_d, w_d, n_d, n_nodes, par, fl);
+      if (bit_words(n_nodes) <= P.lds_words) mark_live_lds(p_d, w_d, n_d, n_nodes, par, fl, nodes);
+      else mark_live(p_d, w_d, n_d, n_nodes, par, fl);
 
       // level offsets: live codes per depth, then running sums
       uint32_t *lv = (uint32_t *)(P.img + P.L.level) + bt.lvl_base;
+      const bool few_levels = L < 256u;
       {
+        // (all but a few of a batch's nodes share a handful of counters: in LDS, when
+        // there are fewer than 256 levels)
+        if (tid < 256) run[tid] = 0u;
+        __syncthreads();
         uint32_t live = 0, int1 = 0, top = 0;
         for (uint32_t c = 1 + tid; c < n_nodes; c += kIgBlock) {
           const uint32_t f = fl[c];
@@ -332,7 +373,10 @@ __global__ __launch_bounds__(kIgBlock) void image_kernel(IgParams P) {
           ++live;
           top = max(top, d);
           if (d == 1u && (f & kHasChild)) ++int1;
-          if (d >= 1u && d <= L) atomicAdd(&lv[d], 1u);
+          if (d >= 1u && d <= L) {
+            if (few_levels) atomicAdd(&run[d], 1u);
+            else atomicAdd(&lv[d], 1u);
+          }
         }
         atomicAdd(&s_live, live);
         atomicAdd(&s_int1, int1);
@@ -343,35 +387,78 @@ __global__ __launch_bounds__(kIgBlock) void image_kernel(IgParams P) {
       carry = 0;
       for (uint32_t d0 = 1; d0 <= L; d0 += kIgBlock) {
         const uint32_t d = d0 + tid;
-        const uint32_t x = d <= L ? lv[d] : 0u;
+        const uint32_t x = d <= L ? few_levels ? run[d] : lv[d] : 0u;
         const uint32_t v = scan_step(x, wsum, carry);
         if (d <= L) lv[d] = v + x;
       }
       __syncthreads();
       if ((L >= 1 ? lv[1] : 0u) != n1) IG_FAIL(TOC_INGEST_CHANGED);
 
-      // D inverted by code: group sizes, their starts, then the entries tuple by
-      // tuple (a code occurs at most once in a tuple, so the entries of one tuple
-      // take the next place of their groups in any order, and every group lists its
-      // entries in the order of D)
-      for (uint32_t c = tid; c < n_nodes; c += kIgBlock) gz[c] = 0u;
-      __syncthreads();
-      for (uint32_t p = tid; p < n_d; p += kIgBlock) atomicAdd(&gz[rd(p_d, p, w_d)], 1u);
+      // D inverted by code, every group's entries in the order of D: group sizes, their
+      // starts, the entries in any order (g holds them for now), then each at its rank
+      // in its group, the entries of the group before it.  A code occurs at most once
+      // in a tuple, so a group has at most n_r entries; where that makes the ranks
+      // dear, the entries are dealt tuple by tuple instead (a barrier per tuple, whose
+      // entries take the next place of their groups in any order: 1000 one-hot batches
+      // took 2.26 ms in all that way; with the ranks, the counts in LDS and twice the
+      // workgroups 1.07 ms).
+      // (counted in LDS, 16 bits a node, when it holds them and no count can reach
+      // 2^16; gz in memory gets the counts)
+      const bool in_lds = (n_nodes + 1u) / 2u <= P.lds_words && n_d < 65536u;
+      auto zero_counts = [&]() {
+        if (in_lds)
+          for (uint32_t x = tid; x < (n_nodes + 1u) / 2u; x += kIgBlock) nodes[x] = 0u;
+        else
+          for (uint32_t c = tid; c < n_nodes; c += kIgBlock) gz[c] = 0u;
+        __syncthreads();
+      };
+      auto count_up = [&](uint32_t c) -> uint32_t {
+        if (in_lds) return atomicAdd(&nodes[c / 2u], 1u << (c % 2u * 16u)) >> (c % 2u * 16u) & 0xffffu;
+        return atomicAdd(&gz[c], 1u);
+      };
+      zero_counts();
+      for (uint32_t p = tid; p < n_d; p += kIgBlock) count_up(rd(p_d, p, w_d));
       __syncthreads();
       carry = 0;
-      for (uint32_t c0 = 0; c0 < n_nodes; c0 += kIgBlock) {
-        const uint32_t c = c0 + tid;
-        const uint32_t v = scan_step(c < n_nodes ? gz[c] : 0u, wsum, carry);
-        if (c < n_nodes) gs[c] = v;
+      {
+        uint32_t most = 0;
+        for (uint32_t c0 = 0; c0 < n_nodes; c0 += kIgBlock) {
+          const uint32_t c = c0 + tid;
+          uint32_t x = 0u;
+          if (c < n_nodes) x = in_lds ? nodes[c / 2u] >> (c % 2u * 16u) & 0xffffu : gz[c];
+          const uint32_t v = scan_step(x, wsum, carry);
+          if (c < n_nodes) {
+            gs[c] = v;
+            if (in_lds) gz[c] = x;
+          }
+          most = max(most, x);
+        }
+        atomicMax(&run[0], most);    // (0 so far: levels start at 1)
       }
-      for (uint32_t c = tid; c < n_nodes; c += kIgBlock) gz[c] = 0u;
       __syncthreads();
-      for (uint32_t r = 0; r < n_r; ++r) {
-        for (uint32_t p = st[r] + tid; p < st[r + 1]; p += kIgBlock) {
+      zero_counts();
+      if (run[0] <= kRankMost) {
+        for (uint32_t p = tid; p < n_d; p += kIgBlock) {
           const uint32_t c = rd(p_d, p, w_d);
-          occ[gs[c] + atomicAdd(&gz[c], 1u)] = p;
+          g[gs[c] + count_up(c)] = p;
         }
         __syncthreads();
+        for (uint32_t e = tid; e < n_d; e += kIgBlock) {
+          const uint32_t p = g[e], c = rd(p_d, p, w_d), ga = gs[c], ge = ga + gz[c];
+          uint32_t rank = 0;
+#pragma unroll 4
+          for (uint32_t x = ga; x < ge; ++x) rank += g[x] < p ? 1u : 0u;
+          occ[ga + rank] = p;
+        }
+        __syncthreads();
+      } else {
+        for (uint32_t r = 0; r < n_r; ++r) {
+          for (uint32_t p = st[r] + tid; p < st[r + 1]; p += kIgBlock) {
+            const uint32_t c = rd(p_d, p, w_d);
+            occ[gs[c] + count_up(c)] = p;
+          }
+          __syncthreads();
+        }
       }
 
       // places of depth-1 codes with children: 0 .. ni-1, in node order
@@ -547,19 +634,37 @@ __global__ __launch_bounds__(kIgBlock) void image_kernel(IgParams P) {
       // codes, counted then summed up to each column (entry m closes the sums)
       uint32_t *cx = (uint32_t *)(P.img + P.L.cols) + b * 4 * ((int64_t)m + 1);
       uint32_t *c_code = cx, *c_occ = cx + (m + 1), *c_tree = cx + 2 * (m + 1), *c_ord = cx + 3 * (m + 1);
-      for (uint32_t q = ni + tid; q < n1; q += kIgBlock) {
-        const uint32_t c = at[atl[q]];
-        atomicAdd(&c_code[cl[c]], 1u);
-        atomicAdd(&c_occ[cl[c]], gz[c]);
+      // (counted in LDS when it holds three words a column)
+      const bool cols_lds = 3u * (m + 1u) <= P.lds_words;
+      if (cols_lds) {
+        for (uint32_t x = tid; x < 3u * (m + 1u); x += kIgBlock) nodes[x] = 0u;
+        __syncthreads();
       }
-      for (uint32_t t = tid; t < ntree; t += kIgBlock) atomicAdd(&c_tree[cl[at[tl[t]]]], 1u);
+      uint32_t *n_occ = nodes + (m + 1u), *n_tr = n_occ + (m + 1u);
+      for (uint32_t q = ni + tid; q < n1; q += kIgBlock) {
+        const uint32_t c = at[atl[q]], j = cl[c];
+        if (cols_lds) {
+          atomicAdd(&nodes[j], 1u);
+          atomicAdd(&n_occ[j], gz[c]);
+        } else {
+          atomicAdd(&c_code[j], 1u);
+          atomicAdd(&c_occ[j], gz[c]);
+        }
+      }
+      for (uint32_t t = tid; t < ntree; t += kIgBlock) {
+        const uint32_t j = cl[at[tl[t]]];
+        if (cols_lds) atomicAdd(&n_tr[j], 1u);
+        else atomicAdd(&c_tree[j], 1u);
+      }
       __syncthreads();
       {
         uint32_t ca = 0, co = 0, ct = 0, mx = 0;
         for (uint32_t j0 = 0; j0 <= m; j0 += kIgBlock) {
           const uint32_t j = j0 + tid;
           const bool in = j <= m;
-          const uint32_t a = in ? c_code[j] : 0u, o = in ? c_occ[j] : 0u, t = in ? c_tree[j] : 0u;
+          uint32_t a = 0u, o = 0u, t = 0u;
+          if (in && cols_lds) a = nodes[j], o = n_occ[j], t = n_tr[j];
+          else if (in) a = c_code[j], o = c_occ[j], t = c_tree[j];
           const uint32_t va = scan_step(a, wsum, ca), vo = scan_step(o, wsum, co);
           const uint32_t vt = scan_step(t, wsum, ct);
           if (in) {
@@ -652,6 +757,14 @@ RangeWs range_ws(int64_t nb, int64_t nodes, int64_t nd, int64_t sort_len, int64_
   return w;
 }
 
+// Workgroups for nb batches: as many as a CU holds four of, when the slots of
+// slot_words words from w.slot on fit the workspace (what the sizes above ask for
+// holds kIgGrid of the largest slots).  The kernels wait for memory most of the time.
+unsigned ig_grid(int64_t nb, const RangeWs &w, int64_t slot_words, size_t ws_bytes) {
+  const int64_t slots = ((int64_t)ws_bytes - w.slot) / (4 * std::max<int64_t>(slot_words, 1));
+  return (unsigned)std::min<int64_t>(nb, std::max<int64_t>(kIgGrid, std::min<int64_t>(slots, kIgGridMost)));
+}
+
 struct Batches {
   const toc_phys_info *info;
   int64_t n;
@@ -676,6 +789,19 @@ RangeWs ws_for(const Batches &B, int64_t b0, int64_t b1, const toc_dev *dev, WsF
   return range_ws(b1 - b0, B.node_off[(size_t)b1] - B.node_off[(size_t)b0],
                   B.d_off[(size_t)b1] - B.d_off[(size_t)b0], sort_len_of(B, b0, b1, dev, what),
                   what == kWsBuild ? 0 : ((int64_t)B.n_cols + 31) / 32);
+}
+
+// LDS words for the nodes of a batch in b0 .. b1-1: 16-bit counts (which also hold
+// the bits) or the bits alone, at most kNodeLds bytes so that four workgroups fit a CU;
+// 0 when neither fits for the largest batch.
+constexpr uint32_t kNodeLds = 24 * 1024;
+uint32_t node_lds_words(const Batches &B, int64_t b0, int64_t b1, bool bits_only) {
+  int64_t n = 1;
+  for (int64_t b = b0; b < b1; ++b) n = std::max<int64_t>(n, B.info[b].n_nodes);
+  if (n > (int64_t)kNodeLds * 4) return 0;
+  const uint32_t counts = ((uint32_t)n + 1) / 2 + 2, bits = bit_words((uint32_t)n);
+  if (!bits_only && 4 * counts <= kNodeLds) return counts;
+  return 4 * bits <= kNodeLds ? bits : 0;
 }
 
 toc_status check_batches(const toc_phys_info *info, int64_t n, int32_t n_cols, Batches &B) {
@@ -835,13 +961,14 @@ toc_status toc_ingest_plan(const void *blobs, const int64_t *blob_off, const toc
       if ((ret = launch_cprime(blobs, blob_off, B, nullptr, b0, b1, w, wb, s, max_rows)) != TOC_OK)
         break;
       const int64_t nb = b1 - b0;
-      const unsigned grid = (unsigned)std::min<int64_t>(nb, kIgGrid);
-      hipLaunchKernelGGL(census_kernel, dim3(grid), dim3(kIgBlock), 0, s, (const uint8_t *)blobs,
+      const unsigned grid = ig_grid(nb, w, ((int64_t)n_cols + 31) / 32, ws_bytes);
+      const uint32_t bits = node_lds_words(B, b0, b1, true);
+      hipLaunchKernelGGL(census_kernel, dim3(grid), dim3(kIgBlock), 4 * bits, s, (const uint8_t *)blobs,
                          (const int64_t *)(wb + w.offs), nb, (uint32_t)n_cols,
                          (const int32_t *)(wb + w.status), (const uint32_t *)(wb + w.parent),
                          (const uint32_t *)(wb + w.col), (const uint32_t *)(wb + w.depth),
                          (uint32_t *)(wb + w.flags), (uint32_t *)(wb + w.slot),
-                         (int64_t *)(wb + w.counts), (int32_t *)(wb + w.status));
+                         (int64_t *)(wb + w.counts), (int32_t *)(wb + w.status), bits);
       if (hipGetLastError() != hipSuccess) {
         ret = fail(TOC_EDEVICE, "census_kernel launch failed");
         break;
@@ -948,12 +1075,15 @@ toc_status toc_ingest_build(toc_dev *dev, const void *blobs, const int64_t *blob
       P.img = img;
       P.L = dev->layout;
       P.status = (int32_t *)(wb + w.status);
-      const size_t lds = 8 * ((size_t)max_rows + 1);
-      if (lds > 64 * 1024 &&
+      // (none beside the offsets of very tall batches, which may need all of the LDS)
+      const size_t rows_lds = 8 * ((size_t)max_rows + 1);
+      P.lds_words = rows_lds > 64 * 1024 ? 0 : node_lds_words(B, b0, b1, false);
+      const size_t lds = rows_lds + 4 * (size_t)P.lds_words;
+      if (lds > 48 * 1024 &&
           hipFuncSetAttribute((const void *)image_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds) != hipSuccess)
         return fail(TOC_EDEVICE, "cannot raise dynamic LDS to %zu bytes", lds);
-      const unsigned grid = (unsigned)std::min<int64_t>(nb, kIgGrid);
+      const unsigned grid = ig_grid(nb, w, 4 * P.sort_len, ws_bytes);
       hipLaunchKernelGGL(image_kernel, dim3(grid), dim3(kIgBlock), lds, s, P);
       if (hipGetLastError() != hipSuccess) return fail(TOC_EDEVICE, "image_kernel launch failed");
       std::vector<int32_t> st((size_t)nb);
