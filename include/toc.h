@@ -265,9 +265,10 @@ toc_status toc_left_mul(const toc_dev *dev, const float *G, int32_t k, int64_t l
 /* Left multiplication without any allocation, for callers that cannot allocate
  * device memory (work captured into a HIP graph, tight serving loops, harnesses
  * that forbid hipMalloc).  The same product as toc_left_mul given the workspace that
- * toc_workspace_size asks for, bit for bit, with no workspace argument: the workspace is a static device buffer of
- * TOC_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on until
- * the process ends (its address is looked up on the first call on each device).
+ * toc_workspace_size asks for, bit for bit, with no workspace argument: the workspace
+ * is a static device buffer of TOC_NOALLOC_SCRATCH_BYTES that the library holds on
+ * every GPU it runs on until the process ends (its address is looked up on the first
+ * call on each device).
  * When the full grid's per-worker slots do not fit in it, fewer persistent
  * workers run (slower, same result).  Calls on one GPU share that buffer: calls
  * that overlap in time on one GPU (other streams, other host threads) race and
