@@ -176,7 +176,10 @@ __device__ int block_radix_sort(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32
 // Per batch, the counts the image layout depends on (written to counts[8 b ..]):
 // live codes, deepest live depth, depth-1 codes with live children, live codes of
 // depth >= 2, nonzeros (the sum of the depths of D's codes: each code decodes to
-// that many pairs), live depth-1 codes, and distinct key columns of live codes.
+// that many pairs), live depth-1 codes, distinct key columns of live codes, and nodes
+// whose column is not beyond their parent's.  Neighbouring codes of a tuple have made a
+// node of C' (the first code's, extended by the second's first pair), so there is none
+// of those exactly when the columns of every tuple increase.
 __global__ __launch_bounds__(kIgBlock) void census_kernel(
     const uint8_t *__restrict__ blobs, const int64_t *__restrict__ offs, int64_t n_batches,
     uint32_t n_cols, const int32_t *__restrict__ cp_status, const uint32_t *__restrict__ parent,
@@ -186,7 +189,7 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
   extern __shared__ uint32_t node_bits[];
   __shared__ Hdr h;
   __shared__ unsigned long long s_nnz;
-  __shared__ uint32_t s_live, s_top, s_int1, s_deep, s_lvl1, s_ucols;
+  __shared__ uint32_t s_live, s_top, s_int1, s_deep, s_lvl1, s_ucols, s_falls;
   const int64_t *node_off = offs + (n_batches + 1);
   const uint32_t ncw = (n_cols + 31) / 32;
   uint32_t *colbits = colbits_all + (int64_t)blockIdx.x * ncw;
@@ -199,7 +202,7 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
       h.err = cp_status[b];
       if (h.err == 0) parse_headers(blob, size, 1 << 30, h);
       s_nnz = 0ull;
-      s_live = s_top = s_int1 = s_deep = s_lvl1 = s_ucols = 0u;
+      s_live = s_top = s_int1 = s_deep = s_lvl1 = s_ucols = s_falls = 0u;
     }
     __syncthreads();
     if (h.err) {
@@ -218,9 +221,10 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
     else mark_live(p_d, w_d, n_d, n_nodes, par, fl);
     for (uint32_t x = threadIdx.x; x < ncw; x += kIgBlock) colbits[x] = 0u;
     __syncthreads();
-    uint32_t live = 0, top = 0, int1 = 0, deep = 0, lvl1 = 0;
+    uint32_t live = 0, top = 0, int1 = 0, deep = 0, lvl1 = 0, falls = 0;
     for (uint32_t c = 1 + threadIdx.x; c < n_nodes; c += kIgBlock) {
-      const uint32_t f = fl[c];
+      const uint32_t f = fl[c], q = par[c];
+      if (q != 0u && cl[c] <= cl[q]) ++falls;
       if (!(f & kLive)) continue;
       const uint32_t d = dep[c];
       ++live;
@@ -240,6 +244,7 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
     atomicAdd(&s_int1, int1);
     atomicAdd(&s_deep, deep);
     atomicAdd(&s_lvl1, lvl1);
+    atomicAdd(&s_falls, falls);
     atomicAdd(&s_nnz, nnz);
     __syncthreads();
     uint32_t u = 0;
@@ -255,7 +260,7 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
       o[4] = (int64_t)s_nnz;
       o[5] = s_lvl1;
       o[6] = s_ucols;
-      o[7] = 0;
+      o[7] = s_falls;
       status[b] = 0;
     }
     __syncthreads();
@@ -996,6 +1001,7 @@ toc_status toc_ingest_plan(const void *blobs, const int64_t *blob_off, const toc
         k.canon = 4 * f.n_codes + 4 * (f.n_rows + 1) + 10 * c[0] + 4 * (c[1] + 1);
         n1[(size_t)b] = c[5];
         nu[(size_t)b] = c[6];
+        if (c[7] != 0) dev->columns_rise = false;
       }
     }
     if (ret == TOC_OK) ret = toc::plan_layout(bc.data(), n_batches, n_cols, 0u, dev);

@@ -191,11 +191,11 @@ __device__ inline void tree_rows(const Batch &t, uint32_t a, uint32_t e, F put) 
 // its subtree: done here once per call, a thread per code, instead of inside the
 // products' pipelines once per tile of columns (there it took half of the dense
 // quantised batches' time).  A column has room for the tuples that hold none of its
-// leaves, so its place needs no scan; a code takes its pairs' places in the column
-// level by level, the lanes of one column with one atomic addition (an addition per
-// code took 590 us for 100 dense quantised batches, counting the subtrees first 112 us,
-// this 97 us).  The order of a column's pairs varies from run to run and does not
-// matter: each fills a tile cell of its own.
+// leaves (a tuple has each of its columns once), so its place needs no scan; a code
+// takes its pairs' places in the column level by level, the lanes of one column with
+// one atomic addition (an addition per code took 590 us for 100 dense quantised
+// batches, counting the subtrees first 112 us, this 97 us).  The order of a column's
+// pairs varies from run to run and does not matter: each fills a tile cell of its own.
 // xn: pairs of each column so far, zero on entry.
 // ---------------------------------------------------------------------------
 constexpr int kExpandThreads = 256;
@@ -224,7 +224,13 @@ __global__ __launch_bounds__(kExpandThreads) void tree_expand_kernel(MfmaImg im,
       o0 = t.to[a], o1 = t.to[a + 1], c0 = t.tch[a], c1 = t.tch[a + 1];
     }
     uint32_t *next = xn + bi * im.n_stride + j;
-    uint2 *w = xpair + bi * im.x_stride + (there ? (int64_t)j * t.n_rows - t.occ[j] : 0);
+    const int64_t place = there ? (int64_t)j * t.n_rows - t.occ[j] : 0;
+    uint2 *const x = xpair + bi * im.x_stride;
+    // (in bounds whatever the bytes that the image was built from hold)
+    auto put = [&](uint32_t at, uint32_t word) {
+      const int64_t o = place + at;
+      if ((uint64_t)o < (uint64_t)im.x_stride) x[o] = make_uint2(word & kRowMask, v);
+    };
     // lanes of one column are neighbours: whether the lane o below is of the same one,
     // and the column's last lane
     bool same[6];
@@ -238,9 +244,9 @@ __global__ __launch_bounds__(kExpandThreads) void tree_expand_kernel(MfmaImg im,
       // one level of every lane's subtree: its places in the column, its first tuples
       // and the next level's places are in flight together
       const uint32_t p0 = o0, n = o1 - o0;
-      uint32_t x[4];
+      uint32_t row[4];
 #pragma unroll
-      for (uint32_t i = 0; i < 4; ++i) x[i] = i < n ? t.ce[p0 + i] : 0u;
+      for (uint32_t i = 0; i < 4; ++i) row[i] = i < n ? t.ce[p0 + i] : 0u;
       const bool more = c0 < c1;
       const uint32_t a = c0 - t.n1 + t.ni, e = c1 - t.n1 + t.ni;
       o0 = o1 = c0 = c1 = 0;
@@ -256,8 +262,8 @@ __global__ __launch_bounds__(kExpandThreads) void tree_expand_kernel(MfmaImg im,
       first = (uint32_t)__shfl((int)first, last_lane, kWave) + (sum - n);
 #pragma unroll
       for (uint32_t i = 0; i < 4; ++i)
-        if (i < n) w[first + i] = make_uint2(x[i] & kRowMask, v);
-      for (uint32_t i = 4; i < n; ++i) w[first + i] = make_uint2(t.ce[p0 + i] & kRowMask, v);
+        if (i < n) put(first + i, row[i]);
+      for (uint32_t i = 4; i < n; ++i) put(first + i, t.ce[p0 + i]);
     }
   }
 }
@@ -998,6 +1004,8 @@ namespace toc {
 bool mfma_suits(const toc_dev *d, int32_t k, bool right) {
   const toc_dev_info &n = d->info;
   if (k < 2 || d->max_rows > 256 || d->max_ucols < 1) return false;
+  // a tile has one cell for a tuple and a column
+  if (!d->columns_rise) return false;
   if (pass_bytes(d, 1) > kLeastBytes) return false;
   const int64_t cells = n.n_rows * d->max_ucols;
   if (n.nnz * 16 < cells) return false;
