@@ -639,8 +639,8 @@ __global__ __launch_bounds__(kIgBlock, 8) void image_kernel(IgParams P) {
       // codes, counted then summed up to each column (entry m closes the sums)
       uint32_t *cx = (uint32_t *)(P.img + P.L.cols) + b * 4 * ((int64_t)m + 1);
       uint32_t *c_code = cx, *c_occ = cx + (m + 1), *c_tree = cx + 2 * (m + 1), *c_ord = cx + 3 * (m + 1);
-      // (counted in LDS when it holds three words a column)
-      const bool cols_lds = 3u * (m + 1u) <= P.lds_words;
+      // (counted in LDS when it holds three words a column; 32 bits would wrap)
+      const bool cols_lds = 3ull * (m + 1ull) <= P.lds_words;
       if (cols_lds) {
         for (uint32_t x = tid; x < 3u * (m + 1u); x += kIgBlock) nodes[x] = 0u;
         __syncthreads();
