@@ -4,17 +4,26 @@
 // The matrix cores run bf16 products with binary32 accumulation at 16 times the
 // vector units' rate, so a batch is expanded on the chip, 32 of its used columns at
 // a time, into LDS tiles of bf16, and never in memory.  Operands keep their 24-bit
-// significands: a binary32 value is split exactly into three bf16 parts,
-// x = x1 + x2 + x3 with |x2| <= 2^-7 |x|, |x3| <= 2^-15 |x|, and a product x.y is the
-// sum of the parts' products x1y1 + x1y2 + x2y1 + x1y3 + x2y2 + x3y1; what is left out
-// is below 2^-22 |x||y| and of both signs (the dense operand's parts are rounded to
-// nearest).  A chunk whose values all have x2 = x3 = 0 (integers below 256, 1.0,
-// sixteenths) takes the three products of x1 alone, an exact shortcut decided from
-// the chunk's own values.
+// significands: a binary32 value is split exactly into three bf16 parts (Henry, Tang and
+// Heinecke, "Leveraging the bfloat16 artificial intelligence datatype for
+// higher-precision computations", ARITH 2019), x = x1 + x2 + x3 with |x2| < 2^-7 |x|,
+// |x3| < 2^-15 |x| (the dense operand's are rounded to nearest: half of these), and a
+// product x.y is the sum of all products of parts but x3y3, which is below 2^-31 |x||y|.
+// With six of them, up to x1y3, x2y2 and x3y1, a sum of one term was off by 1.9e-7 of
+// itself at most, where one fma gives 6.0e-8.  A chunk whose values all have
+// x2 = x3 = 0 (integers below 256, 1.0, sixteenths) takes the three products of x1
+// alone, which are exact; the entries loaded past a column's end are looked at too, so
+// some chunks take eight that need not.
 //
-// Sums are formed in blocks, the small products first: the right product adds the 32
-// terms of a chunk to an output at once, the left product keeps the small products of
-// all tuples apart from the large ones x1y1 until the end.
+// Sums are formed in blocks: the right product adds the 32 terms of a chunk to an output
+// at once, the left product those of all tuples.  Both keep the products of smaller
+// parts apart from the leading ones x1y1 until then: the matrix cores cut a sum off where
+// they add to it instead of rounding it, which with one accumulator for all parts left
+// sums of one term off by 1.1e-7.  Kept apart, sums of one term are as good as the
+// vector kernels' (largest 6.0e-8, RMS 2.5e-8), of two 1.6e-7 at most where those have
+// 1.2e-7 (RMS 3.0e-8 and 2.9e-8), and the products of 250-row batches are closer to
+// 64 bits (2-norm; vector kernels, then these): image-like right 1.1e-7, 8.0e-8, left
+// 1.1e-7, 5.3e-8; dense quantised right 1.6e-7, 1.1e-7, left 1.2e-7, 8.8e-8.
 //
 // Parts of values near the ends of the exponent range would be lost, and an
 // infinity or NaN of the dense operand must not reach tuples without that column
@@ -629,11 +638,13 @@ __global__ __launch_bounds__(kThreads) void left_mfma_kernel(
 #pragma unroll
           for (int pl = 0; pl < 3; ++pl) next[pl] = operand(at + 1, pl);
         }
-        lo[mt] = mfma(a1, g[s][2], lo[mt]);
+        lo[mt] = mfma(a2, g[s][2], lo[mt]);
         hi[mt] = mfma(a1, g[s][0], hi[mt]);
         lo2[mt] = mfma(a1, g[s][1], lo2[mt]);
-        lo[mt] = mfma(a2, g[s][1], lo[mt]);
+        lo[mt] = mfma(a3, g[s][1], lo[mt]);
         lo2[mt] = mfma(a2, g[s][0], lo2[mt]);
+        lo[mt] = mfma(a1, g[s][2], lo[mt]);
+        lo[mt] = mfma(a2, g[s][1], lo[mt]);
         lo[mt] = mfma(a3, g[s][0], lo[mt]);
       }
     }
@@ -824,13 +835,15 @@ __global__ __launch_bounds__(kThreads) void right_mfma_kernel(
           w3[s] = next[s];
           if (n + 1 < NF) next[s] = *(const tile_u32x4 *)(tb + s * kBPlane + (n + 1) * 256);
         }
-        f32x4 sum[4] = {};
+        f32x4 hi[4] = {}, lo[4] = {};
 #pragma unroll
-        for (int s = 2; s >= 0; --s)
+        for (int x = 0; x < 4; ++x) lo[x] = mfma(a[x], w3[2], lo[x]);
 #pragma unroll
-          for (int x = 0; x < 4; ++x) sum[x] = mfma(a[x], w3[s], sum[x]);
+        for (int x = 0; x < 4; ++x) hi[x] = mfma(a[x], w3[0], hi[x]);
 #pragma unroll
-        for (int x = 0; x < 4; ++x) acc[x][n] += sum[x];
+        for (int x = 0; x < 4; ++x) lo[x] = mfma(a[x], w3[1], lo[x]);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) acc[x][n] += hi[x] + lo[x];
       }
     } else {
 #pragma unroll
@@ -845,21 +858,22 @@ __global__ __launch_bounds__(kThreads) void right_mfma_kernel(
           u32x4 w3[3];
 #pragma unroll
           for (int s = 0; s < 3; ++s) w3[s] = *(const tile_u32x4 *)(tb + s * kBPlane + n * 256);
-          f32x4 sum[2] = {};
+          f32x4 hi[2] = {}, lo[2] = {};
+          auto small = [&](int p, int r) {
 #pragma unroll
-          for (int x = 0; x < 2; ++x) sum[x] = mfma(a[x][2], w3[0], sum[x]);
+            for (int x = 0; x < 2; ++x) lo[x] = mfma(a[x][p], w3[r], lo[x]);
+          };
+          small(2, 1);
+          small(1, 2);
+          small(2, 0);
+          small(1, 1);
+          small(0, 2);
+          small(1, 0);
+          small(0, 1);
 #pragma unroll
-          for (int x = 0; x < 2; ++x) sum[x] = mfma(a[x][1], w3[1], sum[x]);
+          for (int x = 0; x < 2; ++x) hi[x] = mfma(a[x][0], w3[0], hi[x]);
 #pragma unroll
-          for (int x = 0; x < 2; ++x) sum[x] = mfma(a[x][0], w3[2], sum[x]);
-#pragma unroll
-          for (int x = 0; x < 2; ++x) sum[x] = mfma(a[x][1], w3[0], sum[x]);
-#pragma unroll
-          for (int x = 0; x < 2; ++x) sum[x] = mfma(a[x][0], w3[1], sum[x]);
-#pragma unroll
-          for (int x = 0; x < 2; ++x) sum[x] = mfma(a[x][0], w3[0], sum[x]);
-#pragma unroll
-          for (int x = 0; x < 2; ++x) acc[xh + x][n] += sum[x];
+          for (int x = 0; x < 2; ++x) acc[xh + x][n] += hi[x] + lo[x];
           __builtin_amdgcn_sched_barrier(0);   // (loads hoisted further ahead spill)
         }
       }
