@@ -176,10 +176,11 @@ __device__ int block_radix_sort(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32
 // Per batch, the counts the image layout depends on (written to counts[8 b ..]):
 // live codes, deepest live depth, depth-1 codes with live children, live codes of
 // depth >= 2, nonzeros (the sum of the depths of D's codes: each code decodes to
-// that many pairs), live depth-1 codes, distinct key columns of live codes, and nodes
-// whose column is not beyond their parent's.  Neighbouring codes of a tuple have made a
-// node of C' (the first code's, extended by the second's first pair), so there is none
-// of those exactly when the columns of every tuple increase.
+// that many pairs), live depth-1 codes, distinct key columns of live codes, and the pairs
+// of D's codes with live children or of depth >= 2, or -1 when a node's column is not
+// beyond its parent's: neighbouring codes of a tuple have made a node of C' (the first
+// code's, extended by the second's first pair), so there is none of those exactly when the
+// columns of every tuple increase.
 __global__ __launch_bounds__(kIgBlock) void census_kernel(
     const uint8_t *__restrict__ blobs, const int64_t *__restrict__ offs, int64_t n_batches,
     uint32_t n_cols, const int32_t *__restrict__ cp_status, const uint32_t *__restrict__ parent,
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
     int64_t *__restrict__ counts, int32_t *__restrict__ status, uint32_t lds_words) {
   extern __shared__ uint32_t node_bits[];
   __shared__ Hdr h;
-  __shared__ unsigned long long s_nnz;
+  __shared__ unsigned long long s_nnz, s_tree;
   __shared__ uint32_t s_live, s_top, s_int1, s_deep, s_lvl1, s_ucols, s_falls;
   const int64_t *node_off = offs + (n_batches + 1);
   const uint32_t ncw = (n_cols + 31) / 32;
@@ -201,7 +202,7 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
     if (threadIdx.x == 0) {
       h.err = cp_status[b];
       if (h.err == 0) parse_headers(blob, size, 1 << 30, h);
-      s_nnz = 0ull;
+      s_nnz = s_tree = 0ull;
       s_live = s_top = s_int1 = s_deep = s_lvl1 = s_ucols = s_falls = 0u;
     }
     __syncthreads();
@@ -237,8 +238,12 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
       }
       atomicOr(&colbits[cl[c] / 32], 1u << (cl[c] % 32));
     }
-    unsigned long long nnz = 0;
-    for (uint32_t p = threadIdx.x; p < n_d; p += kIgBlock) nnz += dep[rd(p_d, p, w_d)];
+    unsigned long long nnz = 0, tree = 0;
+    for (uint32_t p = threadIdx.x; p < n_d; p += kIgBlock) {
+      const uint32_t c = rd(p_d, p, w_d), d = dep[c];
+      nnz += d;
+      if (d > 1u || (fl[c] & kHasChild)) tree += d;
+    }
     atomicAdd(&s_live, live);
     atomicMax(&s_top, top);
     atomicAdd(&s_int1, int1);
@@ -246,6 +251,7 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
     atomicAdd(&s_lvl1, lvl1);
     atomicAdd(&s_falls, falls);
     atomicAdd(&s_nnz, nnz);
+    atomicAdd(&s_tree, tree);
     __syncthreads();
     uint32_t u = 0;
     for (uint32_t x = threadIdx.x; x < ncw; x += kIgBlock) u += (uint32_t)__popc(colbits[x]);
@@ -260,7 +266,7 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
       o[4] = (int64_t)s_nnz;
       o[5] = s_lvl1;
       o[6] = s_ucols;
-      o[7] = s_falls;
+      o[7] = s_falls ? -1 : (int64_t)s_tree;
       status[b] = 0;
     }
     __syncthreads();
@@ -957,7 +963,7 @@ toc_status toc_ingest_plan(const void *blobs, const int64_t *blob_off, const toc
     }
     hipStream_t s = (hipStream_t)stream;
     std::vector<toc::BatchCounts> bc((size_t)n_batches);
-    std::vector<int64_t> n1((size_t)n_batches), nu((size_t)n_batches);
+    std::vector<int64_t> n1((size_t)n_batches), nu((size_t)n_batches), tp((size_t)n_batches);
     for (int64_t b0 = 0, b1 = 0; b0 < n_batches && ret == TOC_OK; b0 = b1) {
       if ((ret = next_range(B, b0, ws_bytes, nullptr, kWsCensus, b1)) != TOC_OK) break;
       const RangeWs w = ws_for(B, b0, b1, nullptr, kWsCensus);
@@ -1001,7 +1007,8 @@ toc_status toc_ingest_plan(const void *blobs, const int64_t *blob_off, const toc
         k.canon = 4 * f.n_codes + 4 * (f.n_rows + 1) + 10 * c[0] + 4 * (c[1] + 1);
         n1[(size_t)b] = c[5];
         nu[(size_t)b] = c[6];
-        if (c[7] != 0) dev->columns_rise = false;
+        tp[(size_t)b] = std::max<int64_t>(c[7], 0);
+        if (c[7] < 0) dev->columns_rise = false;
       }
     }
     if (ret == TOC_OK) ret = toc::plan_layout(bc.data(), n_batches, n_cols, 0u, dev);
@@ -1013,6 +1020,7 @@ toc_status toc_ingest_plan(const void *blobs, const int64_t *blob_off, const toc
       dev->batches[(size_t)b].n_lvl1 = (int32_t)n1[(size_t)b];
       dev->batches[(size_t)b].n_ucols = (int32_t)nu[(size_t)b];
     }
+    dev->tree_pairs = std::move(tp);
     toc::finish_image(dev);
     dev->phys.assign(info, info + n_batches);
     dev->pending = true;

@@ -38,6 +38,10 @@ struct toc_dev {
   // whether the columns of every tuple increase (the encoders check it; physical bytes
   // from elsewhere need not hold to it)
   bool columns_rise = true;
+  // per batch, the pairs that its tree codes (codes with children or of depth >= 2) stand
+  // for in its tuples, and the most of a batch (after build)
+  std::vector<int64_t> tree_pairs;
+  int64_t max_tree_pairs = 0;
   int64_t max_keylinks = 0;        // most keys plus deep links of a batch (after build)
   int64_t max_deep = 0, max_tree = 0, max_d = 0;
   // most deep codes of two batches b, b + 8 with b / 8 even (the batch pairs of
@@ -100,8 +104,10 @@ toc_status plan_layout(const BatchCounts *bc, int64_t n_batches, int32_t n_cols,
 // Products with k >= 2 on the matrix cores (toc_mfma.hip).  mfma_suits: whether they are
 // the faster ones for an image and an operand of k columns; mfma_workspace: the
 // workspace bytes they ask for; mfma_fits: whether a call (row stride ld of W or out,
-// workspace) can take them.  The arguments of the other two are those of toc_left_mul /
-// toc_right_mul, already checked (stream: a hipStream_t).
+// workspace) takes them.  A workspace of TOC_NOALLOC_SCRATCH_BYTES always does where
+// they suit, so toc_left_mul_noalloc and toc_left_mul choose alike.  The arguments of the
+// other two are those of toc_left_mul / toc_right_mul, already checked (stream: a
+// hipStream_t).
 bool mfma_suits(const toc_dev *d, int32_t k, bool right);
 size_t mfma_workspace(const toc_dev *d);
 bool mfma_fits(const toc_dev *d, int32_t k, bool right, int64_t ld, const void *ws, size_t ws_bytes);

@@ -44,6 +44,7 @@ constexpr int kXcd = 8;
 constexpr int kThreads = 512;                 // 8 waves, 2 per SIMD: 256 registers each
 constexpr int kChunk = 32;                    // used columns per LDS tile
 constexpr uint32_t kRowMask = 0x3fffffffu;    // row of a leaf occurrence word
+constexpr uint32_t kRoot = 0xffffffffu;       // parent of a code of depth 1
 constexpr uint32_t kLeftRow = (kChunk + 4) * 16;   // bytes of a slot row of the left product's tile
 constexpr uint32_t kSpare = kWave * 4;         // bytes after a plane: a word per lane without an entry
 
@@ -112,19 +113,19 @@ struct MfmaImg {
   const toc_key *key;
   const toc_link *link;
   const uint32_t *span, *dcodes, *centry, *cval, *occ_off, *tlist, *cols, *tchild;
-  // expanded tree codes (tree_expand_kernel) of batches b0 ..: pairs per column, and
-  // the pairs (tuple, value bits), x_stride of them to a batch, column j's from
-  // j n_rows - (leaf occurrences of the columns before it)
-  const uint32_t *xn;
+  // expanded tree codes (tree_expand_kernel) of batches b0 ..: the pairs (tuple, value
+  // bits) column by column, room for x_stride of them to a batch, and each column's
+  // first (and the end), xoff_stride words to a batch
+  const uint32_t *xoff;
   const uint2 *xpair;
-  int64_t b0, n_stride, x_stride;
+  int64_t b0, xoff_stride, x_stride;
 };
 
 // One batch's column entries and tree, in wave-uniform registers.
 struct Batch {
   const uint32_t *ce, *cv;       // entries and their values
   __amdgpu_buffer_rsrc_t ce_res, cv_res, x_res;   // range-checked; x: expanded pairs
-  const uint32_t *xn;            // expanded pairs per column
+  const uint32_t *xoff;          // per column: expanded pairs before it
   const toc_key *key;
   const uint32_t *occ, *tf;      // per column: leaf occurrences before it, tree-list start
   const uint32_t *order;         // columns, most entries first, those without last
@@ -163,7 +164,7 @@ __device__ inline Batch load_batch(const MfmaImg &im, int64_t b, int m) {
   t.x_res = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint2 *>(im.xpair + (b - im.b0) * im.x_stride), (short)0, (int)(im.x_stride * 8),
       0x00020000);
-  t.xn = im.xn + (b - im.b0) * im.n_stride;
+  t.xoff = im.xoff + (b - im.b0) * im.xoff_stride;
   t.key = im.key + code_base;
   return t;
 }
@@ -196,85 +197,159 @@ __device__ inline void tree_rows(const Batch &t, uint32_t a, uint32_t e, F put) 
 // The tree codes of the batches, expanded column by column: for every column the
 // tuples whose sequences pass through one of its tree codes, with the code's value.  They
 // are a small part of a batch's pairs (2 % of an image-like batch, 14 % of a dense
-// quantised one), but each is found through up to two dependent loads per level of
-// its subtree: done here once per call, a thread per code, instead of inside the
-// products' pipelines once per tile of columns (there it took half of the dense
-// quantised batches' time).  A column has room for the tuples that hold none of its
-// leaves (a tuple has each of its columns once), so its place needs no scan; a code
-// takes its pairs' places in the column level by level, the lanes of one column with
-// one atomic addition (an addition per code took 590 us for 100 dense quantised
-// batches, counting the subtrees first 112 us, this 97 us).  The order of a column's
-// pairs varies from run to run and does not matter: each fills a tile cell of its own.
-// xn: pairs of each column so far, zero on entry.
+// quantised one), but each is found through dependent loads: done here once per call
+// instead of inside the products' pipelines once per tile of columns (there it took half
+// of the dense quantised batches' time).  A workgroup takes a batch and walks from every
+// tree code that tuples hold up to the root, twice: first the pairs of each column are
+// counted, in LDS, then, from the counts' running sums, written.  So a batch takes the
+// room of its pairs (a place for every cell took 25 to 150 times as much, and no scan).
+// kExpandCodes walks of a thread are in flight at a time.  The order of a column's pairs
+// varies from run to run and does not matter: each fills a tile cell of its own.
+//
+// What bounds it is a cache line per lane of nearly every load and store, at one line a
+// clock and CU, and the chain of loads of a deep code: so the tree codes (a tree row's
+// parent row, column and value, 8 bytes) are first copied to LDS, where they fit.  Few
+// batches of many codes are shared by `parts` workgroups each: every one counts all
+// pairs and writes those of its part of the codes.
 // ---------------------------------------------------------------------------
-constexpr int kExpandThreads = 256;
+constexpr int kExpandThreads = 1024;
+constexpr int kExpandCodes = 4;
 
-__global__ __launch_bounds__(256) void tree_zero_kernel(u32x4 *__restrict__ xn, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) xn[i] = u32x4{0, 0, 0, 0};
-}
-
-__global__ __launch_bounds__(kExpandThreads) void tree_expand_kernel(MfmaImg im, int m, int blocks,
-                                                                     uint32_t *__restrict__ xn,
+template <bool LDS>
+__global__ __launch_bounds__(kExpandThreads) void tree_expand_kernel(MfmaImg im, int m, int max_tree,
+                                                                     int parts,
+                                                                     uint32_t *__restrict__ xoff,
                                                                      uint2 *__restrict__ xpair) {
-  const int64_t bi = blockIdx.x / blocks;
-  const Batch t = load_batch(im, im.b0 + bi, m);
-  const int lane = threadIdx.x % kWave;
-  const uint32_t n_tree = t.n_tree;
-  for (uint32_t s0 = (uint32_t)(blockIdx.x % blocks) * kExpandThreads; s0 < n_tree;
-       s0 += (uint32_t)blocks * kExpandThreads) {
-    const uint32_t s = s0 + threadIdx.x;
-    const bool there = s < n_tree;
-    uint32_t j = 0xffffffffu, v = 0, o0 = 0, o1 = 0, c0 = 0, c1 = 0;
-    if (there) {
-      const uint32_t y = t.tl[s], a = y < t.ni ? y : y - t.n1 + t.ni;
-      v = t.cv[t.tbase + s];
-      j = t.key[y].col;
-      o0 = t.to[a], o1 = t.to[a + 1], c0 = t.tch[a], c1 = t.tch[a + 1];
-    }
-    uint32_t *next = xn + bi * im.n_stride + j;
-    const int64_t place = there ? (int64_t)j * t.n_rows - t.occ[j] : 0;
-    uint2 *const x = xpair + bi * im.x_stride;
-    // (in bounds whatever the bytes that the image was built from hold)
-    auto put = [&](uint32_t at, uint32_t word) {
-      const int64_t o = place + at;
-      if ((uint64_t)o < (uint64_t)im.x_stride) x[o] = make_uint2(word & kRowMask, v);
-    };
-    // lanes of one column are neighbours: whether the lane o below is of the same one,
-    // and the column's last lane
-    bool same[6];
+  extern __shared__ uint32_t next[];            // per column: its pairs, then its next place
+  __shared__ uint32_t wave_sum[kExpandThreads / kWave];
+  uint32_t *before = next + m;                  // (parts > 1) per column: pairs of the parts before
+  uint32_t *up_col = next + (parts > 1 ? 2 * m : m), *key_val = up_col + max_tree;   // (up 0xffff: the root)
+  const int64_t bi = blockIdx.x / parts, b = im.b0 + bi;
+  const uint32_t part = blockIdx.x % parts;
+  const Batch t = load_batch(im, b, m);
+  const toc_link *link = im.link + (uniform64(im.batches[b].deep_base) - (int64_t)t.n1);
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  // tree row h: its column and value, and the tree row of its parent
+  auto node = [&](uint32_t h, uint32_t &up, uint32_t &col, uint32_t &val) {
+    const uint32_t c = h < t.ni ? h : h - t.ni + t.n1;
+    const toc_key k = t.key[c];
+    const uint32_t p = c >= t.n1 ? link[c].parent : kRoot;
+    up = p == kRoot || p < t.n1 ? p : p - t.n1 + t.ni;
+    col = k.col;
+    val = __float_as_uint(k.val);
+  };
+  const uint32_t lo = part * t.n_tree / parts, hi = (part + 1) * t.n_tree / parts;
+  // put(u, column, value bits, first occurrence, their number) for every code on the way up
+  // to the root from every one of tree codes a .. e-1 that tuples hold, the u-th of the
+  // thread's in flight; begin() before each set of those
+  auto walk = [&](uint32_t a, uint32_t e, auto begin, auto put) {
+    for (uint32_t h0 = a + tid; h0 < e; h0 += kExpandCodes * kExpandThreads) {
+      uint32_t o[kExpandCodes], n[kExpandCodes], h[kExpandCodes];
 #pragma unroll
-    for (int o = 0; o < 6; ++o)
-      same[o] = (uint32_t)__shfl_up((int)j, 1 << o, kWave) == j && lane >= 1 << o;
-    const uint32_t above = (uint32_t)__shfl_down((int)j, 1, kWave);
-    const bool last = lane == kWave - 1 || above != j;
-    const int last_lane = lane + __ffsll((unsigned long long)(__ballot(last) >> lane)) - 1;
-    while (__any(o0 < o1 || c0 < c1)) {
-      // one level of every lane's subtree: its places in the column, its first tuples
-      // and the next level's places are in flight together
-      const uint32_t p0 = o0, n = o1 - o0;
-      uint32_t row[4];
-#pragma unroll
-      for (uint32_t i = 0; i < 4; ++i) row[i] = i < n ? t.ce[p0 + i] : 0u;
-      const bool more = c0 < c1;
-      const uint32_t a = c0 - t.n1 + t.ni, e = c1 - t.n1 + t.ni;
-      o0 = o1 = c0 = c1 = 0;
-      if (more) o0 = t.to[a], o1 = t.to[e], c0 = t.tch[a], c1 = t.tch[e];
-      uint32_t sum = n;
-#pragma unroll
-      for (int o = 0; o < 6; ++o) {
-        const uint32_t u = (uint32_t)__shfl_up((int)sum, 1 << o, kWave);
-        if (same[o]) sum += u;
+      for (int u = 0; u < kExpandCodes; ++u) {
+        h[u] = h0 + (uint32_t)(u * kExpandThreads);
+        o[u] = h[u] < e ? t.to[h[u]] : 0u;
+        n[u] = h[u] < e ? t.to[h[u] + 1] - o[u] : 0u;
+        if (n[u] == 0u) h[u] = kRoot;
       }
-      uint32_t first = 0;
-      if (last && sum) first = atomicAdd(next, sum);
-      first = (uint32_t)__shfl((int)first, last_lane, kWave) + (sum - n);
+      begin(o, n);
+      while (true) {
+        uint32_t up[kExpandCodes], col[kExpandCodes], val[kExpandCodes];
+        bool any = false;
 #pragma unroll
-      for (uint32_t i = 0; i < 4; ++i)
-        if (i < n) put(first + i, row[i]);
-      for (uint32_t i = 4; i < n; ++i) put(first + i, t.ce[p0 + i]);
+        for (int u = 0; u < kExpandCodes; ++u) {
+          up[u] = kRoot;
+          col[u] = val[u] = 0u;
+          if (h[u] == kRoot) continue;
+          any = true;
+          if (LDS) {
+            const uint32_t w = up_col[h[u]];
+            up[u] = w >> 16 == 0xffffu ? kRoot : w >> 16;
+            col[u] = w & 0xffffu;
+            val[u] = key_val[h[u]];
+          } else {
+            node(h[u], up[u], col[u], val[u]);
+          }
+        }
+        if (!any) break;
+#pragma unroll
+        for (int u = 0; u < kExpandCodes; ++u) {
+          if (h[u] != kRoot) put(u, col[u], val[u], o[u], n[u]);
+          h[u] = up[u];
+        }
+      }
     }
+  };
+  for (int j = tid; j < (parts > 1 ? 2 * m : m); j += kExpandThreads) next[j] = 0u;
+  if (LDS)
+    for (uint32_t h = tid; h < t.n_tree; h += kExpandThreads) {
+      uint32_t up, col;
+      node(h, up, col, key_val[h]);
+      up_col[h] = up << 16 | col;
+    }
+  __syncthreads();
+  auto none = [](auto &, auto &) {};
+  auto count = [&](int, uint32_t j, uint32_t, uint32_t, uint32_t n) { atomicAdd(&next[j], n); };
+  if (parts > 1) {
+    walk(0, lo, none, [&](int, uint32_t j, uint32_t, uint32_t, uint32_t n) { atomicAdd(&before[j], n); });
+    walk(lo, t.n_tree, none, count);
+    __syncthreads();
+    for (int j = tid; j < m; j += kExpandThreads) next[j] += before[j];
+  } else {
+    walk(0, t.n_tree, none, count);
   }
+  __syncthreads();
+  // running sums: a thread's columns are neighbours
+  const int per = (m + kExpandThreads - 1) / kExpandThreads;
+  const int j0 = min(m, tid * per), j1 = min(m, j0 + per);
+  uint32_t sum = 0;
+  for (int j = j0; j < j1; ++j) sum += next[j];
+  uint32_t at0 = sum;
+#pragma unroll
+  for (int s = 1; s < kWave; s *= 2) {
+    const uint32_t u = (uint32_t)__shfl_up((int)at0, s, kWave);
+    if (lane >= s) at0 += u;
+  }
+  if (lane == kWave - 1) wave_sum[wave] = at0;
+  __syncthreads();
+  at0 -= sum;
+  for (int w = 0; w < wave; ++w) at0 += wave_sum[w];
+  uint32_t *off = xoff + bi * im.xoff_stride;
+  for (int j = j0; j < j1; ++j) {
+    const uint32_t n = next[j];
+    next[j] = at0 + (parts > 1 ? before[j] : 0u);
+    if (part == 0) off[j] = at0;
+    at0 += n;
+  }
+  if (part == 0 && tid == kExpandThreads - 1) off[m] = at0;   // (its columns, if any, are the last)
+  __syncthreads();
+  uint2 *const x = xpair + bi * im.x_stride;
+  // (in bounds whatever the bytes that the image was built from hold)
+  auto store = [&](uint32_t at, uint32_t row, uint32_t bits) {
+    if (at < (uint64_t)im.x_stride) x[at] = make_uint2(row & kRowMask, bits);
+  };
+  uint32_t row[kExpandCodes][2];                     // the first tuples of each code
+  walk(
+      lo, hi,
+      [&](auto &o, auto &n) {
+#pragma unroll
+        for (int u = 0; u < kExpandCodes; ++u)
+#pragma unroll
+          for (uint32_t i = 0; i < 2; ++i) row[u][i] = i < n[u] ? t.ce[o[u] + i] : 0u;
+      },
+      [&](int u, uint32_t j, uint32_t bits, uint32_t o, uint32_t n) {
+        const uint32_t at = atomicAdd(&next[j], n);
+        store(at, row[u][0], bits);
+        if (n > 1) store(at + 1, row[u][1], bits);
+        for (uint32_t i0 = 2; i0 < n; i0 += 4) {
+          uint32_t r[4];
+#pragma unroll
+          for (uint32_t i = 0; i < 4; ++i) r[i] = i0 + i < n ? t.ce[o + i0 + i] : 0u;
+#pragma unroll
+          for (uint32_t i = 0; i < 4; ++i)
+            if (i0 + i < n) store(at + i0 + i, r[i], bits);
+        }
+      });
 }
 
 // Where the used columns of the chunks in flight find their entries: written by the
@@ -288,19 +363,20 @@ struct Ring {
 constexpr uint32_t kNone = 0x80000000u;
 
 struct RingLoad {
-  uint32_t jn, jp, l0, l1, x;
+  uint32_t jn, jp, l0, l1, x0, x1;
   __device__ void places(const Batch &t) {
-    l0 = l1 = x = 0;
+    l0 = l1 = x0 = x1 = 0;
     if (jp != 0xffffffffu) {
       l0 = t.occ[jp];
       l1 = t.occ[jp + 1];
-      x = t.xn[jp];
+      x0 = t.xoff[jp];
+      x1 = t.xoff[jp + 1];
     }
   }
   __device__ void publish(const Batch &t, Ring &ring, int slot, uint32_t i, uint32_t row_bytes) {
     ring.off[slot][i] = jp == 0xffffffffu ? kNone : jp * row_bytes;
-    ring.at[slot][i] = u32x4{l0, l1 - l0, jp * (uint32_t)t.n_rows - l0, x};
-    uint32_t a = (l1 - l0 + 15u) / 16u, b = (x + 15u) / 16u;
+    ring.at[slot][i] = u32x4{l0, l1 - l0, x0, x1 - x0};
+    uint32_t a = (l1 - l0 + 15u) / 16u, b = (x1 - x0 + 15u) / 16u;
     a = max(a, (uint32_t)__shfl_xor((int)a, 1, kWave));
     b = max(b, (uint32_t)__shfl_xor((int)b, 1, kWave));
     a = max(a, (uint32_t)__shfl_xor((int)a, 2, kWave));
@@ -471,7 +547,8 @@ struct Feed {
 // tuples each) fall into different banks.
 // ---------------------------------------------------------------------------
 template <int KS>
-__global__ __launch_bounds__(kThreads) void left_mfma_kernel(
+// (64 tuples: 128 registers, so that two workgroups share a CU)
+__global__ __launch_bounds__(kThreads, KS == 2 ? 4 : 2) void left_mfma_kernel(
     MfmaImg im, int64_t nb, int n_tiles, int m, const float *__restrict__ G, int64_t ldg,
     int k, float *__restrict__ out, int64_t ldo, int accumulate) {
   constexpr uint32_t kPlane = KS * 4 * kLeftRow + kSpare;
@@ -951,46 +1028,78 @@ MfmaImg image_of(const toc_dev *d) {
   return im;
 }
 
-// Workspace of a run of batches: the expanded pairs per column (m words a batch,
-// rounded up to 16 bytes), then room for a pair in every cell of every batch.
-size_t counters_bytes(int64_t n, int64_t m) { return (size_t)(n * ((m + 3) / 4 * 16)); }
+// Workspace of a run of n batches: their columns' first pairs (m + 1 words a batch,
+// rounded up to 16 bytes), then room for the pairs of the batch with the most.
+int64_t offsets_words(const toc_dev *d) { return ((int64_t)d->info.n_cols + 4) / 4 * 4; }
 size_t pass_bytes(const toc_dev *d, int64_t n) {
-  const int64_t m = d->info.n_cols;
-  return counters_bytes(n, m) + (size_t)(8 * n * m * d->max_rows);
+  return (size_t)(n * (4 * offsets_words(d) + 8 * std::max<int64_t>(d->max_tree_pairs, 1)));
 }
-constexpr size_t kPassBytes = (size_t)1 << 30;   // workspace asked for at most
-constexpr size_t kLeastBytes = (size_t)32 << 20;   // holds any batch; less is not used
+// Asked for at most; more is used when given.
+constexpr size_t kPassBytes = TOC_NOALLOC_SCRATCH_BYTES;
+constexpr int64_t kExpandCols = 16384;            // columns whose counts the LDS holds
+constexpr size_t kExpandLds = 152 * 1024;
 
-// Per pass of batches: their tree codes expanded into the workspace, then `kernel`
-// over all (batch, tile) pairs, the tiles of a batch on one XCD.
+// Batches full of deep codes (dense quantised ones).
+bool many_deep(const toc_dev *d) {
+  const toc_dev_info &n = d->info;
+  return n.nnz * 2 >= n.n_rows * d->max_ucols && n.n_deep * 32 > n.n_stored;
+}
+
+// The batches that a pass has to hold: enough for 192 pairs of batch and 128-column tile,
+// three quarters of the chip's CUs (1,200 image-like batches at k = 300, left: passes of
+// 21 batches 3.8 ms, of 42 1.9 ms, one pass 0.87 ms, vector kernel 1.3 ms), or for 64
+// where the vector kernels are four times slower (200 dense quantised batches at k = 200,
+// left: passes of 34 batches 1.5 ms, one pass 0.53 ms, vector kernel 2.7 ms).
+int64_t least_batches(const toc_dev *d, int32_t k, bool right) {
+  const int64_t pairs = many_deep(d) || (right && k < 4) ? 64 : 192, tiles = (k + 127) / 128;
+  return std::min(d->info.n_batches, (pairs + tiles - 1) / tiles);
+}
+
+// Workgroups that share a batch's tree codes in a pass of n batches: one where a workgroup
+// has them all in flight, else as many as the chip's CUs allow (dense quantised batches of
+// 15,005 tree codes, k = 200, right and left with one workgroup, then with several: one
+// batch 214 -> 196 and 227 -> 207 us, 100 223 -> 204 and 275 -> 260; 200 batches with two
+// each 487 -> 525 and 529 -> 550).
+int expand_parts(const toc_dev *d, int64_t n) {
+  return d->max_tree <= kExpandCodes * kExpandThreads
+             ? 1
+             : (int)std::max<int64_t>(1, std::min<int64_t>(256 / n, 8));
+}
+
+// Per pass of batches, of one size: their tree codes expanded into the workspace, then
+// `kernel` over all (batch, tile) pairs, the tiles of a batch on one XCD.
 template <typename K, typename... Args>
 toc_status run(const char *name, K kernel, size_t lds, const toc_dev *d, int n_tiles, void *ws,
                size_t ws_bytes, hipStream_t s, Args... args) {
-  if (hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)lds) != hipSuccess)
-    return fail(TOC_EDEVICE, "cannot raise dynamic LDS to %zu bytes", lds);
   const int64_t nb = d->info.n_batches, m = d->info.n_cols;
-  for (int64_t b0 = 0; b0 < nb;) {
-    const int blocks =
-        (int)std::max<int64_t>(1, std::min<int64_t>(64, (d->max_tree + kExpandThreads - 1) / kExpandThreads));
-    const int64_t most = std::max<int64_t>(1, ((int64_t)1 << 21) / std::max(blocks, n_tiles));
-    const int64_t n = std::min({nb - b0, most, (int64_t)(ws_bytes / pass_bytes(d, 1))});
+  // the tree codes in LDS, where it holds them beside the columns' counts; see expand_parts
+  const size_t lds_t = 8 * (size_t)m + 8 * (size_t)d->max_tree;
+  const bool tree_lds = d->max_tree < 0xffff && lds_t <= kExpandLds;
+  const size_t lds_x = tree_lds ? lds_t : 8 * (size_t)m;
+  const auto expand = tree_lds ? tree_expand_kernel<true> : tree_expand_kernel<false>;
+  auto allow = [](const void *f, size_t bytes) {
+    return bytes <= 48 * 1024 ||
+           hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
+  };
+  if (!allow((const void *)kernel, lds) || !allow((const void *)expand, lds_x))
+    return fail(TOC_EDEVICE, "cannot raise dynamic LDS to %zu bytes", std::max(lds, lds_x));
+  const int64_t most = std::min<int64_t>(((int64_t)1 << 21) / n_tiles, (int64_t)(ws_bytes / pass_bytes(d, 1)));
+  const int64_t n_passes = (nb + most - 1) / most, per = (nb + n_passes - 1) / n_passes;
+  for (int64_t b0 = 0; b0 < nb; b0 += per) {
+    const int64_t n = std::min(nb - b0, per);
     MfmaImg im = image_of(d);
     im.b0 = b0;
-    im.n_stride = (m + 3) / 4 * 4;
-    im.x_stride = m * d->max_rows;
-    uint32_t *xn = (uint32_t *)ws;
-    uint2 *xpair = (uint2 *)((uint8_t *)ws + counters_bytes(n, m));
-    im.xn = xn;
+    im.xoff_stride = offsets_words(d);
+    im.x_stride = std::max<int64_t>(d->max_tree_pairs, 1);
+    uint32_t *xoff = (uint32_t *)ws;
+    uint2 *xpair = (uint2 *)(xoff + n * im.xoff_stride);
+    im.xoff = xoff;
     im.xpair = xpair;
-    const int64_t zeros = (int64_t)(counters_bytes(n, m) / 16);
-    hipLaunchKernelGGL(tree_zero_kernel, dim3((unsigned)((zeros + 255) / 256)), dim3(256), 0, s,
-                       (u32x4 *)xn, zeros);
-    hipLaunchKernelGGL(tree_expand_kernel, dim3((unsigned)(n * blocks)), dim3(kExpandThreads), 0, s,
-                       im, (int)m, blocks, xn, xpair);
+    const int parts = tree_lds ? expand_parts(d, n) : 1;
+    hipLaunchKernelGGL(expand, dim3((unsigned)(n * parts)), dim3(kExpandThreads), lds_x, s, im, (int)m,
+                       (int)d->max_tree, parts, xoff, xpair);
     const unsigned grid = (unsigned)((n + kXcd - 1) / kXcd * kXcd * n_tiles);
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, s, im, n, n_tiles, args...);
-    b0 += n;
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(TOC_EDEVICE, "%s: %s", name, hipGetErrorString(e));
@@ -1020,12 +1129,12 @@ bool mfma_suits(const toc_dev *d, int32_t k, bool right) {
   if (k < 2 || d->max_rows > 256 || d->max_ucols < 1) return false;
   // a tile has one cell for a tuple and a column
   if (!d->columns_rise) return false;
-  if (pass_bytes(d, 1) > kLeastBytes) return false;
+  if (n.n_cols > kExpandCols || pass_bytes(d, least_batches(d, k, right)) > kPassBytes) return false;
   const int64_t cells = n.n_rows * d->max_ucols;
   if (n.nnz * 16 < cells) return false;
   if (right && k < 4) return true;
   if (right && n.n_codes * 10 < n.nnz * 9) return false;
-  if (n.nnz * 2 >= cells && n.n_deep * 32 > n.n_stored) return true;
+  if (many_deep(d)) return true;
   return k > 64 && n.n_batches * ((k + 63) / 64) >= 300;
 }
 
@@ -1037,7 +1146,7 @@ bool mfma_fits(const toc_dev *d, int32_t k, bool right, int64_t ld, const void *
                size_t ws_bytes) {
   // 32-bit byte offsets into W and a batch's block of out
   if (!mfma_suits(d, k, right) || (int64_t)d->info.n_cols * ld >= ((int64_t)1 << 28)) return false;
-  return ws && ((uintptr_t)ws & 15) == 0 && ws_bytes >= std::min(mfma_workspace(d), kLeastBytes);
+  return ws && ((uintptr_t)ws & 15) == 0 && ws_bytes >= pass_bytes(d, least_batches(d, k, right));
 }
 
 toc_status left_mfma(const toc_dev *d, const float *G, int32_t k, int64_t ldg, float *out, int64_t ldo,

@@ -12,6 +12,7 @@ import pytest
 
 import oracle as O
 import paper_1702_06943_amd as T
+from matrix_path import took_matrix_cores, tree_pairs
 from workloads import Batches, tiny_batch
 
 torch = pytest.importorskip("torch")
@@ -38,12 +39,6 @@ def _upload(B, flags=0):
 def _ws(dev, op, k):
     n, _ = T.toc_workspace_size(dev, op, k)
     return torch.full((max(n, 4) // 4,), float("nan"), device=DEV)
-
-
-def _asks_for_expansion(dev, op, k):
-    """The matrix-core path is the only one whose workspace covers every cell."""
-    info = T.toc_dev_info_get(dev)
-    return T.toc_workspace_size(dev, op, k)[0] >= 8 * info["n_rows"] * info["n_cols"]
 
 
 def _rows(B, b):
@@ -83,7 +78,6 @@ def _check_left(B, out, G, init=None):
 def test_left(rows, cols, k, kw, accumulate):
     B = _batches(rows, cols, 7000 + cols, **kw)
     dev = _upload(B)
-    assert _asks_for_expansion(dev, T.TOC_OP_LEFT, k)
     rng = np.random.default_rng(cols * k)
     G = rng.standard_normal((int(B.row_off[-1]), k)).astype(np.float32)
     Gd = torch.zeros((len(G), k + 3), device=DEV)
@@ -91,7 +85,9 @@ def test_left(rows, cols, k, kw, accumulate):
     init = rng.standard_normal((B.n_batches * cols, k)).astype(np.float32)
     out = torch.full((len(init), k + 5), float("nan"), device=DEV)
     out[:, :k] = torch.from_numpy(init)
-    T.toc_left_mul(dev, Gd[:, :k], out[:, :k], accumulate, _ws(dev, T.TOC_OP_LEFT, k))
+    ws = _ws(dev, T.TOC_OP_LEFT, k)
+    T.toc_left_mul(dev, Gd[:, :k], out[:, :k], accumulate, ws)
+    assert took_matrix_cores(ws, tree_pairs(B), cols)
     _check_left(B, out[:, :k].cpu().numpy(), G, init if accumulate else None)
     assert torch.isnan(out[:, k:]).all()          # the padding stays untouched
     # the same bits without a workspace of the caller's
@@ -113,31 +109,80 @@ def test_left(rows, cols, k, kw, accumulate):
 def test_right(rows, cols, k, kw):
     B = _batches(rows, cols, 8000 + cols, **kw)
     dev = _upload(B)
-    assert _asks_for_expansion(dev, T.TOC_OP_RIGHT, k)
     W = np.random.default_rng(cols * k).standard_normal((cols, k)).astype(np.float32)
     Wd = torch.zeros((cols, k + 2), device=DEV)
     Wd[:, :k] = torch.from_numpy(W)
     R = torch.full((int(B.row_off[-1]), k + 1), float("nan"), device=DEV)
-    T.toc_right_mul(dev, Wd[:, :k], R[:, :k], _ws(dev, T.TOC_OP_RIGHT, k))
+    ws = _ws(dev, T.TOC_OP_RIGHT, k)
+    T.toc_right_mul(dev, Wd[:, :k], R[:, :k], ws)
+    assert took_matrix_cores(ws, tree_pairs(B), cols)
     _check_right(B, R[:, :k].cpu().numpy(), W)
     assert torch.isnan(R[:, k:]).all()
 
 
-def test_dead_codes_and_small_workspace():
-    """An image that keeps unused codes, and a workspace too small for the expansion
-    (the general kernels take the call)."""
-    B = _batches([200, 90], 45, 8800, density=0.9, n_values=3, prefix_copy=0.6)
-    k = 20
-    G = np.random.default_rng(1).standard_normal((290, k)).astype(np.float32)
-    Gd = torch.from_numpy(G).to(DEV)
+def test_dead_codes_and_other_workspaces():
+    """An image that keeps unused codes; and workspaces that the matrix-core kernels do not
+    take (none, too small, not 16-byte aligned), whose calls the general kernels take."""
+    B = _batches([64, 63], 33, 8800, density=0.9, n_values=3, prefix_copy=0.6)
+    rng = np.random.default_rng(1)
+    G = rng.standard_normal((127, 16)).astype(np.float32)
+    W = rng.standard_normal((33, 3)).astype(np.float32)
+    Gd, Wd = torch.from_numpy(G).to(DEV), torch.from_numpy(W).to(DEV)
     for flags in (0, T.TOC_UPLOAD_KEEP_DEAD):
         dev = _upload(B, flags)
-        n, least = T.toc_workspace_size(dev, T.TOC_OP_LEFT, k)
-        for size in (n, least):
-            out = torch.full((2 * 45, k), float("nan"), device=DEV)
-            ws = torch.empty(size, dtype=torch.uint8, device=DEV) if size else None
+        pairs = tree_pairs(B, flags)
+        n, least = T.toc_workspace_size(dev, T.TOC_OP_LEFT, 16)
+        need = 2 * 4 * 36 + 2 * 8 * int(pairs.max())     # offsets and pairs of both batches
+        assert n >= need and (least == 0 or flags)     # (with all codes, the tables need memory)
+        base = torch.full((n + 64,), 255, dtype=torch.uint8, device=DEV)
+        others = [(None, False), (base[:need - 16], False), (base[4:4 + n], False)]
+        for ws, matrix in [(base[:n], True)] + (others if least == 0 else []):
+            base.fill_(255)
+            out = torch.full((2 * 33, 16), float("nan"), device=DEV)
             T.toc_left_mul(dev, Gd, out, False, ws)
+            assert took_matrix_cores(base if ws is None else ws, pairs, 33) == matrix
             _check_left(B, out.cpu().numpy(), G)
+        n, least = T.toc_workspace_size(dev, T.TOC_OP_RIGHT, 3)
+        base = torch.full((max(n, least) + 64,), 255, dtype=torch.uint8, device=DEV)
+        for size, matrix in ((n, True), (least, least >= need)):
+            base.fill_(255)
+            R = torch.full((127, 3), float("nan"), device=DEV)
+            T.toc_right_mul(dev, Wd, R, base[:size])
+            assert took_matrix_cores(base[:size], pairs, 33) == matrix
+            _check_right(B, R.cpu().numpy(), W)
+
+
+@pytest.mark.parametrize("left", [False, True])
+def test_passes_of_a_smaller_workspace(left):
+    """A workspace for fewer batches than the image has: passes of nearly one size, the same
+    bits; and where a pass would not fill the chip, the general kernels."""
+    kw = dict(n_values=400, prefix_copy=0.0) if left else dict(n_values=3, prefix_copy=0.6)
+    B = _batches([70, 66, 90, 128] * 60 + [100], 40, 8850, density=0.9, **kw)
+    dev, k, n = _upload(B), 300 if left else 3, int(B.row_off[-1])
+    pairs = tree_pairs(B)
+    X = np.random.default_rng(2).standard_normal((n if left else 40, k)).astype(np.float32)
+    Xd = torch.from_numpy(X).to(DEV)
+    one = 4 * 44 + 8 * int(pairs.max())
+    outs = []
+    for batches in (241, 100, 64, 63):          # (64 are the least that a pass may have)
+        ws = torch.full((batches * one + 15,), 255, dtype=torch.uint8, device=DEV)
+        out = torch.full((241 * 40 if left else n, k), float("nan"), device=DEV)
+        if left:
+            T.toc_left_mul(dev, Xd, out, False, ws)
+        else:
+            T.toc_right_mul(dev, Xd, out, ws)
+        outs.append(out)
+        # the last pass's sums: the batches are dealt evenly over the passes
+        per = -(-241 // -(-241 // batches))
+        last = pairs[(241 - 1) // per * per:]
+        assert took_matrix_cores(ws, last, 40) == (batches >= 64)
+    for out in (outs[0], outs[3]):
+        (_check_left if left else _check_right)(B, out.cpu().numpy(), X)
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    if left:
+        out = torch.full((241 * 40, k), float("nan"), device=DEV)
+        T.toc_left_mul_noalloc(dev, Xd, out, False)
+        assert torch.equal(outs[0], out)
 
 
 @pytest.mark.parametrize("bad", [np.inf, np.nan, 1e-30, 1e30, 3e38])
@@ -146,7 +191,6 @@ def test_operands_outside_the_split(bad):
     k = 2
     B = _batches([70, 130], 37, 8900, density=0.6, n_values=6, prefix_copy=0.4)
     dev = _upload(B)
-    assert _asks_for_expansion(dev, T.TOC_OP_RIGHT, k)
     rng = np.random.default_rng(5)
     W = rng.standard_normal((37, k)).astype(np.float32)
     G = rng.standard_normal((200, k)).astype(np.float32)
@@ -155,8 +199,12 @@ def test_operands_outside_the_split(bad):
     G[150] = bad
     R = torch.empty((200, k), device=DEV)
     out = torch.empty((2 * 37, k), device=DEV)
-    T.toc_right_mul(dev, torch.from_numpy(W).to(DEV), R, _ws(dev, T.TOC_OP_RIGHT, k))
-    T.toc_left_mul(dev, torch.from_numpy(G).to(DEV), out, False, _ws(dev, T.TOC_OP_LEFT, k))
+    ws = _ws(dev, T.TOC_OP_RIGHT, k)
+    T.toc_right_mul(dev, torch.from_numpy(W).to(DEV), R, ws)
+    assert took_matrix_cores(ws, tree_pairs(B), B.n_cols)
+    ws = _ws(dev, T.TOC_OP_LEFT, k)
+    T.toc_left_mul(dev, torch.from_numpy(G).to(DEV), out, False, ws)
+    assert took_matrix_cores(ws, tree_pairs(B), B.n_cols)
     R, out = R.cpu().numpy(), out.cpu().numpy()
     for b in range(2):
         r0, r1 = int(B.row_off[b]), int(B.row_off[b + 1])
@@ -185,7 +233,11 @@ def test_values_outside_the_split(scale):
     G = rng.standard_normal((106, k)).astype(np.float32)
     R = torch.empty((106, k), device=DEV)
     out = torch.empty((70, k), device=DEV)
-    T.toc_right_mul(dev, torch.from_numpy(W).to(DEV), R, _ws(dev, T.TOC_OP_RIGHT, k))
-    T.toc_left_mul(dev, torch.from_numpy(G).to(DEV), out, False, _ws(dev, T.TOC_OP_LEFT, k))
+    ws = _ws(dev, T.TOC_OP_RIGHT, k)
+    T.toc_right_mul(dev, torch.from_numpy(W).to(DEV), R, ws)
+    assert took_matrix_cores(ws, tree_pairs(B), B.n_cols)
+    ws = _ws(dev, T.TOC_OP_LEFT, k)
+    T.toc_left_mul(dev, torch.from_numpy(G).to(DEV), out, False, ws)
+    assert took_matrix_cores(ws, tree_pairs(B), B.n_cols)
     _check_right(B, R.cpu().numpy(), W)
     _check_left(B, out.cpu().numpy(), G)

@@ -328,3 +328,18 @@ def test_mlp_host_checks():
     st = T.lib().toc_mlp_epoch(hdev.handle, 0, 2, 8, 3, 2, dummy, dummy, dummy, dummy, dummy,
                                dummy, dummy, C.c_float(0.1), dummy, 1 << 20, None)
     assert st == T.TOC_EINVAL
+
+
+def test_products_ask_for_no_more_than_their_tables():
+    """80 image-like batches at k = 300: the matrix-core kernels' workspace holds the pairs
+    of tree codes, less than the general kernels' tables (14 and 28 MB), and is bounded
+    by the static buffer of toc_left_mul_noalloc."""
+    B = config_batches("c3", 0, 8)
+    encs = T.toc_encode_batches(B.n_rows, B.n_cols, B.rowptr, B.col, B.val) * 10
+    buf = np.zeros(T.toc_upload_size(encs, T.TOC_UPLOAD_HOST), np.uint8)
+    dev = T.toc_upload(encs, buf, T.TOC_UPLOAD_HOST)
+    for op in (T.TOC_OP_RIGHT, T.TOC_OP_LEFT):
+        asked, least = T.toc_workspace_size(dev, op, 300)
+        assert asked == least
+    # (right products of 2 columns: the general kernels' table is of one batch)
+    assert T.toc_workspace_size(dev, T.TOC_OP_RIGHT, 2)[0] <= 80 * 16384
