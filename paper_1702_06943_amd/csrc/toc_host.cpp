@@ -590,6 +590,8 @@ toc_status write_batch(const toc_enc *e, int64_t b, uint32_t flags, const toc_la
     for (int64_t k = 0; k < m; ++k) c_ord[k] = (uint32_t)S.keys[k];
     c_ord[m] = 0;
     tree_pairs = e->nnz - (int64_t)c_occ[m];   // (a leaf's occurrence is one pair)
+    for (uint32_t bits : e->I_bits)
+      if (!mfma_value(bits)) tree_pairs = -1;
     // columns that are the key column of some stored code (a leaf or a tree code)
     int32_t u = 0;
     for (int64_t j = 0; j < m; ++j)
@@ -828,7 +830,8 @@ void finish_image(toc_dev *dev) {
   dev->max_ucols = 0;
   dev->max_keylinks = 0;
   dev->max_tree_pairs = 0;
-  for (int64_t n : dev->tree_pairs) dev->max_tree_pairs = std::max(dev->max_tree_pairs, n);
+  for (int64_t n : dev->tree_pairs)
+    dev->max_tree_pairs = n < 0 || dev->max_tree_pairs < 0 ? -1 : std::max(dev->max_tree_pairs, n);
   for (const toc_batch &bt : dev->batches) {
     dev->max_ucols = std::max(dev->max_ucols, bt.n_ucols);
     dev->max_keylinks = std::max<int64_t>(dev->max_keylinks, 2 * (int64_t)bt.n_codes - bt.n_lvl1);

@@ -178,19 +178,21 @@ __device__ int block_radix_sort(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32
 // depth >= 2, nonzeros (the sum of the depths of D's codes: each code decodes to
 // that many pairs), live depth-1 codes, distinct key columns of live codes, and the pairs
 // of D's codes with live children or of depth >= 2, or -1 when a node's column is not
-// beyond its parent's: neighbouring codes of a tuple have made a node of C' (the first
-// code's, extended by the second's first pair), so there is none of those exactly when the
-// columns of every tuple increase.
+// beyond its parent's or a value is not one that the matrix-core products take.
+// (Neighbouring codes of a tuple have made a node of C', the first code's extended by the
+// second's first pair, so no node's column is amiss exactly when the columns of every
+// tuple increase.)
 __global__ __launch_bounds__(kIgBlock) void census_kernel(
     const uint8_t *__restrict__ blobs, const int64_t *__restrict__ offs, int64_t n_batches,
     uint32_t n_cols, const int32_t *__restrict__ cp_status, const uint32_t *__restrict__ parent,
-    const uint32_t *__restrict__ col, const uint32_t *__restrict__ depth,
+    const uint32_t *__restrict__ col, const uint32_t *__restrict__ val,
+    const uint32_t *__restrict__ depth,
     uint32_t *__restrict__ flags_all, uint32_t *__restrict__ colbits_all,
     int64_t *__restrict__ counts, int32_t *__restrict__ status, uint32_t lds_words) {
   extern __shared__ uint32_t node_bits[];
   __shared__ Hdr h;
   __shared__ unsigned long long s_nnz, s_tree;
-  __shared__ uint32_t s_live, s_top, s_int1, s_deep, s_lvl1, s_ucols, s_falls;
+  __shared__ uint32_t s_live, s_top, s_int1, s_deep, s_lvl1, s_ucols, s_other;
   const int64_t *node_off = offs + (n_batches + 1);
   const uint32_t ncw = (n_cols + 31) / 32;
   uint32_t *colbits = colbits_all + (int64_t)blockIdx.x * ncw;
@@ -203,7 +205,7 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
       h.err = cp_status[b];
       if (h.err == 0) parse_headers(blob, size, 1 << 30, h);
       s_nnz = s_tree = 0ull;
-      s_live = s_top = s_int1 = s_deep = s_lvl1 = s_ucols = s_falls = 0u;
+      s_live = s_top = s_int1 = s_deep = s_lvl1 = s_ucols = s_other = 0u;
     }
     __syncthreads();
     if (h.err) {
@@ -222,10 +224,10 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
     else mark_live(p_d, w_d, n_d, n_nodes, par, fl);
     for (uint32_t x = threadIdx.x; x < ncw; x += kIgBlock) colbits[x] = 0u;
     __syncthreads();
-    uint32_t live = 0, top = 0, int1 = 0, deep = 0, lvl1 = 0, falls = 0;
+    uint32_t live = 0, top = 0, int1 = 0, deep = 0, lvl1 = 0, other = 0;
     for (uint32_t c = 1 + threadIdx.x; c < n_nodes; c += kIgBlock) {
       const uint32_t f = fl[c], q = par[c];
-      if (q != 0u && cl[c] <= cl[q]) ++falls;
+      if (q != 0u ? cl[c] <= cl[q] : !toc::mfma_value(val[no + c])) ++other;
       if (!(f & kLive)) continue;
       const uint32_t d = dep[c];
       ++live;
@@ -249,7 +251,7 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
     atomicAdd(&s_int1, int1);
     atomicAdd(&s_deep, deep);
     atomicAdd(&s_lvl1, lvl1);
-    atomicAdd(&s_falls, falls);
+    atomicAdd(&s_other, other);
     atomicAdd(&s_nnz, nnz);
     atomicAdd(&s_tree, tree);
     __syncthreads();
@@ -266,7 +268,7 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
       o[4] = (int64_t)s_nnz;
       o[5] = s_lvl1;
       o[6] = s_ucols;
-      o[7] = s_falls ? -1 : (int64_t)s_tree;
+      o[7] = s_other ? -1 : (int64_t)s_tree;
       status[b] = 0;
     }
     __syncthreads();
@@ -977,7 +979,8 @@ toc_status toc_ingest_plan(const void *blobs, const int64_t *blob_off, const toc
       hipLaunchKernelGGL(census_kernel, dim3(grid), dim3(kIgBlock), 4 * bits, s, (const uint8_t *)blobs,
                          (const int64_t *)(wb + w.offs), nb, (uint32_t)n_cols,
                          (const int32_t *)(wb + w.status), (const uint32_t *)(wb + w.parent),
-                         (const uint32_t *)(wb + w.col), (const uint32_t *)(wb + w.depth),
+                         (const uint32_t *)(wb + w.col), (const uint32_t *)(wb + w.val),
+                         (const uint32_t *)(wb + w.depth),
                          (uint32_t *)(wb + w.flags), (uint32_t *)(wb + w.slot),
                          (int64_t *)(wb + w.counts), (int32_t *)(wb + w.status), bits);
       if (hipGetLastError() != hipSuccess) {
@@ -1007,8 +1010,7 @@ toc_status toc_ingest_plan(const void *blobs, const int64_t *blob_off, const toc
         k.canon = 4 * f.n_codes + 4 * (f.n_rows + 1) + 10 * c[0] + 4 * (c[1] + 1);
         n1[(size_t)b] = c[5];
         nu[(size_t)b] = c[6];
-        tp[(size_t)b] = std::max<int64_t>(c[7], 0);
-        if (c[7] < 0) dev->columns_rise = false;
+        tp[(size_t)b] = c[7];
       }
     }
     if (ret == TOC_OK) ret = toc::plan_layout(bc.data(), n_batches, n_cols, 0u, dev);

@@ -35,11 +35,11 @@ struct toc_dev {
   std::vector<toc_batch> batches;  // host copy of the batch table
   int32_t max_rows = 0, max_codes = 0, max_levels = 0;
   int32_t max_ucols = 0;           // most distinct key columns of a batch (after build)
-  // whether the columns of every tuple increase (the encoders check it; physical bytes
-  // from elsewhere need not hold to it)
-  bool columns_rise = true;
   // per batch, the pairs that its tree codes (codes with children or of depth >= 2) stand
-  // for in its tuples, and the most of a batch (after build)
+  // for in its tuples, or -1 where the matrix-core products do not take it: its tuples'
+  // columns do not all increase (the encoders check that; physical bytes from elsewhere
+  // need not hold to it) or a value is outside kMfmaValLo .. kMfmaValHi; and the most of a
+  // batch, or -1 (after build)
   std::vector<int64_t> tree_pairs;
   int64_t max_tree_pairs = 0;
   int64_t max_keylinks = 0;        // most keys plus deep links of a batch (after build)
@@ -108,6 +108,12 @@ toc_status plan_layout(const BatchCounts *bc, int64_t n_batches, int32_t n_cols,
 // they suit, so toc_left_mul_noalloc and toc_left_mul choose alike.  The arguments of the
 // other two are those of toc_left_mul / toc_right_mul, already checked (stream: a
 // hipStream_t).
+constexpr uint32_t kMfmaValLo = (127 - 32) << 23;   // bits of the least and largest nonzero |value|
+constexpr uint32_t kMfmaValHi = (127 + 50) << 23;
+constexpr bool mfma_value(uint32_t bits) {
+  const uint32_t a = bits & 0x7fffffffu;
+  return a == 0u || (a >= kMfmaValLo && a <= kMfmaValHi);
+}
 bool mfma_suits(const toc_dev *d, int32_t k, bool right);
 size_t mfma_workspace(const toc_dev *d);
 bool mfma_fits(const toc_dev *d, int32_t k, bool right, int64_t ld, const void *ws, size_t ws_bytes);

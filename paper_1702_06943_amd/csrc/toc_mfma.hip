@@ -28,7 +28,14 @@
 // Parts of values near the ends of the exponent range would be lost, and an
 // infinity or NaN of the dense operand must not reach tuples without that column
 // (0 times infinity): a tile whose operands hold a non-finite value, or a nonzero
-// one outside the ranges below, is computed term by term in binary32 instead.
+// one outside the ranges below, is computed term by term in binary32 instead.  The
+// ranges hold what occurs: an image with values outside theirs stays with the vector
+// kernels (toc_map_values can still move some out), and the dense operand is scaled,
+// G column by column, so that its smallest nonzero value may be 2^-129 of the column's
+// largest (saturated gradients; 400 image-like batches at k = 300 with 1 % of 1e-25
+// took 12.9 ms while these went term by term, 0.3 now).  What is left is dear: with an
+// infinity in one row of G that call takes 0.6 ms, in one row of W 1.0 ms, with 1 % of W
+// beyond its range 4.7 ms (vector kernels 0.48 and 0.42 ms).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -45,14 +52,18 @@ constexpr int kThreads = 512;                 // 8 waves, 2 per SIMD: 256 regist
 constexpr int kChunk = 32;                    // used columns per LDS tile
 constexpr uint32_t kRowMask = 0x3fffffffu;    // row of a leaf occurrence word
 constexpr uint32_t kRoot = 0xffffffffu;       // parent of a code of depth 1
+constexpr int kExpandCols = 16384;            // columns whose counts the LDS holds
 constexpr uint32_t kLeftRow = (kChunk + 4) * 16;   // bytes of a slot row of the left product's tile
 constexpr uint32_t kSpare = kWave * 4;         // bytes after a plane: a word per lane without an entry
 
-// |x| of the compressed values in [2^-32, 2^50], of the dense operand in
-// [2^-70, 2^60], zeros apart: every part and product is then a normal number or
-// below 2^-24 of its sum's terms, and no sum overflows.
-constexpr uint32_t kValLo = (127 - 32) << 23, kValHi = (127 + 50) << 23;
-constexpr uint32_t kDenseLo = (127 - 70) << 23, kDenseHi = (127 + 60) << 23;
+// |x| of the compressed values in [2^-32, 2^50], of the scaled dense operand in
+// [2^-62, 2^68), zeros apart: products are then at least 2^-94, so that what parts and
+// products lose below the smallest normal number 2^-126 is below 2^-32 of them, and no
+// sum of 256 overflows.  G is scaled column by column, W by 2^30 (to [2^-92, 2^38)).
+constexpr uint32_t kValLo = toc::kMfmaValLo, kValHi = toc::kMfmaValHi;
+constexpr int kDenseTop = 68;
+constexpr float kDenseLo = 0x1p-62f, kWUp = 0x1p30f;
+constexpr uint32_t kWLo = (127 - 62 - 30) << 23, kWHi = ((127 + kDenseTop - 30) << 23) - 1;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -169,27 +180,34 @@ __device__ inline Batch load_batch(const MfmaImg &im, int64_t b, int m) {
   return t;
 }
 
-// Calls put(row) for every tuple whose sequence passes through tree rows a .. e-1 (codes
-// of one level) or their descendants.  The descendants one level down are
-// consecutive codes and so are their occurrences, so each level is one stretch of
-// entries.
+// The pairs of a column's tree codes, in a fixed order, by a wave: lane l walks the
+// subtree of the l-th code (its own occurrences, then each level's below it: the
+// descendants one level down are consecutive codes and so are their occurrences), all
+// lanes a step at a time; put(row, value bits) for each pair, uniform.
 template <typename F>
-__device__ inline void tree_rows(const Batch &t, uint32_t a, uint32_t e, F put) {
-  uint32_t o0 = t.to[a], o1 = t.to[e], c0 = t.tch[a], c1 = t.tch[e];
-  for (;;) {
-    // the next level's places and this level's first tuples in flight together
-    const uint32_t x0 = o0 < o1 ? t.ce[o0] : 0u, x1 = o0 + 1 < o1 ? t.ce[o0 + 1] : 0u;
-    const uint32_t p0 = o0, p1 = o1;
-    const bool more = c0 < c1;
-    if (more) {
-      a = c0 - t.n1 + t.ni;
-      e = c1 - t.n1 + t.ni;
-      o0 = t.to[a], o1 = t.to[e], c0 = t.tch[a], c1 = t.tch[e];
+__device__ inline void tree_pairs(const Batch &t, uint32_t s0, uint32_t s1, F put) {
+  const uint32_t lane = threadIdx.x % kWave;
+  for (; s0 < s1; s0 += kWave) {
+    uint32_t v = 0, o = 0, oe = 0, c = 0, ce = 0;
+    if (s0 + lane < s1) {
+      const uint32_t y = t.tl[s0 + lane], a = y < t.ni ? y : y - t.n1 + t.ni;
+      v = t.cv[t.tbase + s0 + lane];
+      o = t.to[a], oe = t.to[a + 1], c = t.tch[a], ce = t.tch[a + 1];
     }
-    if (p0 < p1) put(x0 & kRowMask);
-    if (p0 + 1 < p1) put(x1 & kRowMask);
-    for (uint32_t o = p0 + 2; o < p1; ++o) put(t.ce[o] & kRowMask);
-    if (!more) break;
+    while (__any(o < oe || c < ce)) {
+      const bool on = o < oe;
+      const uint32_t row = on ? t.ce[o] & kRowMask : 0u;
+      if (on) {
+        ++o;
+      } else if (c < ce) {
+        const uint32_t a = c - t.n1 + t.ni, e = ce - t.n1 + t.ni;
+        o = t.to[a], oe = t.to[e], c = t.tch[a], ce = t.tch[e];
+      }
+      for (uint64_t m = __ballot(on); m; m &= m - 1) {
+        const int l = __builtin_ctzll(m);
+        put(__builtin_amdgcn_readlane((int)row, l), __builtin_amdgcn_readlane((int)v, l));
+      }
+    }
   }
 }
 
@@ -555,6 +573,7 @@ __global__ __launch_bounds__(kThreads, KS == 2 ? 4 : 2) void left_mfma_kernel(
   extern __shared__ __align__(16) char lds[];   // [2 buffers][3 planes][kPlane]
   __shared__ __align__(16) Ring ring;
   __shared__ uint32_t parts[4], bad[4], bad_g;  // of chunk c at c % 4
+  __shared__ uint32_t slow[kExpandCols / kChunk / 32 + 1];   // a bit per chunk left to the end; any
   const int64_t i = blockIdx.x / kXcd;
   const int64_t b = im.b0 + (i / n_tiles) * kXcd + blockIdx.x % kXcd;
   if (b >= im.b0 + nb) return;
@@ -594,29 +613,46 @@ __global__ __launch_bounds__(kThreads, KS == 2 ? 4 : 2) void left_mfma_kernel(
 
   if (threadIdx.x < 4) parts[threadIdx.x] = bad[threadIdx.x] = 0;
   if (threadIdx.x == 0) bad_g = 0;
+  constexpr int kSlow = kExpandCols / kChunk / 32;
+  if (threadIdx.x <= kSlow) slow[threadIdx.x] = 0;
   RingLoad index;
   index.start(t, ring, (uint32_t)ldo * 4u);
   const uint32_t kk = (uint32_t)(wave * 4 + grp);
   Feed<2 * KS> feed;
 
-  // G: lane holds tuples 32 s + 8 grp .. + 7 of column q
+  // G: lane holds tuples 32 s + 8 grp .. + 7 of column q, scaled by 2^shift so that the
+  // column's largest value is in the topmost binade
   u32x4 g[KS][3];
   Range range;
+  int shift;
+  {
+    float x[KS][8];
 #pragma unroll
-  for (int s = 0; s < KS; ++s) {
-    float x[8];
+    for (int s = 0; s < KS; ++s) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int r = 32 * s + 8 * grp + e;
-      const bool ok = r < t.n_rows && q < k;
-      const float y = Gb[ok ? (int64_t)r * ldg + q : 0];
-      x[e] = ok ? y : 0.0f;
-      range.add(__float_as_uint(x[e]));
+      for (int e = 0; e < 8; ++e) {
+        const int r = 32 * s + 8 * grp + e;
+        const bool ok = r < t.n_rows && q < k;
+        const float y = Gb[ok ? (int64_t)r * ldg + q : 0];
+        x[s][e] = ok ? y : 0.0f;
+        range.add(__float_as_uint(x[s][e]));
+      }
     }
-    split8(x, g[s]);
+    // (the four lanes of a column)
+    uint32_t top = max(range.hi, (uint32_t)__shfl_xor((int)range.hi, 16, kWave));
+    top = max(top, (uint32_t)__shfl_xor((int)top, 32, kWave));
+    shift = top ? kDenseTop - 1 + 127 - (int)(top >> 23) : 0;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[s][e] = ldexpf(x[s][e], shift);
+      split8(x[s], g[s]);
+    }
   }
   __syncthreads();
-  if (range.outside(kDenseLo, kDenseHi)) bad_g = 1;
+  if (range.hi >= 0x7f800000u ||
+      (range.hi && fabsf(ldexpf(__uint_as_float(range.lo + 1u), shift)) < kDenseLo))
+    bad_g = 1;
   feed.load(t, ring, 0, kk, sub);
 
   const auto ores = __builtin_amdgcn_make_buffer_rsrc(
@@ -725,43 +761,17 @@ __global__ __launch_bounds__(kThreads, KS == 2 ? 4 : 2) void left_mfma_kernel(
         lo[mt] = mfma(a3, g[s][0], lo[mt]);
       }
     }
-      const bool slow = __builtin_amdgcn_readfirstlane((int)(bad[c & 3] | bad_g)) != 0;
-      if (!slow) {
-        res_chunk = c;
+    if (__builtin_amdgcn_readfirstlane((int)(bad[c & 3] | bad_g)) == 0) {
+      res_chunk = c;
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+      for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) res[mt][e] = hi[mt][e] + (lo[mt][e] + lo2[mt][e]);
-      } else {
-        // term by term, a wave per column and 64 columns of G at a time
-        for (int i4 = 0; i4 < 4; ++i4) {
-          const uint32_t at = (uint32_t)c * kChunk + (uint32_t)(wave * 4 + i4);
-          if (at >= t.n_used) break;
-          const uint32_t j = t.order[at];
-          for (int h = 0; h < 128; h += kWave) {
-            const int qq = qz + h + lane;
-            const float *Gq = Gb + min(qq, k - 1);
-            float sum = 0.0f, part = 0.0f;
-            uint32_t n = 0;
-            auto term = [&](uint32_t row, float v) {
-              part = fmaf(v, Gq[(int64_t)row * ldg], part);
-              if ((++n & 15u) == 0) sum += part, part = 0.0f;
-            };
-            for (uint32_t o = t.occ[j]; o < t.occ[j + 1]; ++o)
-              term(t.ce[o] & kRowMask, __uint_as_float(t.cv[o]));
-            for (uint32_t s = t.tf[j]; s < t.tf[j + 1]; ++s) {
-              const float v = __uint_as_float(t.cv[t.tbase + s]);
-              const uint32_t y = t.tl[s], a = y < t.ni ? y : y - t.n1 + t.ni;
-              tree_rows(t, a, a + 1, [&](uint32_t row) { term(row, v); });
-            }
-            sum += part;
-            if (qq < k) {
-              float *o = ob + (int64_t)j * ldo + qq;
-              *o = accumulate ? *o + sum : sum;
-            }
-          }
-        }
-      }
+        for (int e = 0; e < 4; ++e)
+          res[mt][e] = ldexpf(hi[mt][e] + (lo[mt][e] + lo2[mt][e]), -shift);
+    } else if (threadIdx.x == 0) {
+      slow[c / 32] |= 1u << (c % 32);
+      slow[kSlow] = 1;
+    }
   };
   for (int c = -1; c < n_chunks; ++c) {
     if (c >= 0) consume(c);
@@ -770,6 +780,68 @@ __global__ __launch_bounds__(kThreads, KS == 2 ? 4 : 2) void left_mfma_kernel(
   }
   put_out();
   zero_rest();
+  if (!__builtin_amdgcn_readfirstlane((int)slow[kSlow])) return;
+  // The chunks left, term by term: 64 columns of G at a time in LDS, a wave per column of
+  // A, its leaf occurrences 64 at a time and then its tree codes' pairs.
+  float *Gs = (float *)lds;
+  for (int h = 0; h < 128 && qz + h < k; h += kWave) {
+    const int qq = qz + h + lane;
+    __syncthreads();
+    for (int r = wave; r < t.n_rows; r += kThreads / kWave)
+      Gs[r * kWave + lane] = Gb[(int64_t)r * ldg + min(qq, k - 1)];
+    __syncthreads();
+    for (int c = 0; c < n_chunks; ++c) {
+      if (!((uint32_t)__builtin_amdgcn_readfirstlane((int)slow[c / 32]) >> (c % 32) & 1u)) continue;
+      // (the wave's four columns' first entries are loaded together)
+      uint32_t j[4], o[4], end[4];
+      int row[4], v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t at = (uint32_t)c * kChunk + (uint32_t)(wave * 4 + i);
+        j[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)t.order[min(at, t.n_used - 1)]);
+      }
+      auto load = [&](int i) {
+        const uint32_t x = min(o[i] + (uint32_t)lane, max(end[i], 1u) - 1);
+        row[i] = (int)(t.ce[x] & kRowMask) * kWave;
+        v[i] = (int)t.cv[x];
+      };
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] = t.occ[j[i]], end[i] = t.occ[j[i] + 1];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) load(i);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if ((uint32_t)c * kChunk + (uint32_t)(wave * 4 + i) >= t.n_used) break;
+        float sum = 0.0f, part = 0.0f;
+        uint32_t n = 0;
+        auto term = [&](int x, float y) {
+          part = fmaf(__int_as_float(x), y, part);
+          if ((++n & 15u) == 0) sum += part, part = 0.0f;
+        };
+        while (o[i] < end[i]) {
+          const int count = (int)min(end[i] - o[i], (uint32_t)kWave);
+          int u = 0;
+          for (; u + 16 <= count; u += 16) {
+            float y[16];
+#pragma unroll
+            for (int x = 0; x < 16; ++x) y[x] = Gs[__builtin_amdgcn_readlane(row[i], u + x) + lane];
+#pragma unroll
+            for (int x = 0; x < 16; ++x) term(__builtin_amdgcn_readlane(v[i], u + x), y[x]);
+          }
+          for (; u < count; ++u)
+            term(__builtin_amdgcn_readlane(v[i], u), Gs[__builtin_amdgcn_readlane(row[i], u) + lane]);
+          o[i] += kWave;
+          if (o[i] < end[i]) load(i);
+        }
+        tree_pairs(t, t.tf[j[i]], t.tf[j[i] + 1], [&](int r, int x) { term(x, Gs[r * kWave + lane]); });
+        sum += part;
+        if (qq < k) {
+          float *p = ob + (int64_t)j[i] * ldo + qq;
+          *p = accumulate ? *p + sum : sum;
+        }
+      }
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -841,7 +913,10 @@ __global__ __launch_bounds__(kThreads) void right_mfma_kernel(
       if (task < 4 * N) {
         u32x4 p[3];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) range.add(__float_as_uint(w[e][r]));
+        for (int r = 0; r < 8; ++r) {
+          range.add(__float_as_uint(w[e][r]));
+          w[e][r] *= kWUp;
+        }
         split8(w[e], p);
 #pragma unroll
         for (int s = 0; s < 3; ++s) *(u32x4 *)(tile + s * kBPlane + task * 16) = p[s];
@@ -966,7 +1041,7 @@ __global__ __launch_bounds__(kThreads) void right_mfma_kernel(
     produce(c);
     __syncthreads();
   }
-  if (out_of_range || range.outside(kDenseLo, kDenseHi)) bad = 1;
+  if (out_of_range || range.outside(kWLo, kWHi)) bad = 1;
   __syncthreads();
   float *Rb = R + t.row_base * ldr;
   if (!bad) {
@@ -978,34 +1053,63 @@ __global__ __launch_bounds__(kThreads) void right_mfma_kernel(
 #pragma unroll
         for (int n = 0; n < NF; ++n) {
           const int q = q0 + (wn * NF + n) * 16 + sub;
-          if (r < t.n_rows && q < k) Rb[(int64_t)r * ldr + q] = acc[x][n][e];
+          if (r < t.n_rows && q < k) Rb[(int64_t)r * ldr + q] = acc[x][n][e] * (1.0f / kWUp);
         }
       }
     }
     return;
   }
-  // term by term: a wave per tuple, each code's chain walked to the root
+  // term by term: a wave per tuple, a lane per code, all walked to the root together; the
+  // rows of W of eight pairs are loaded together
   const toc_batch *bp = im.batches + b;
   const uint32_t *span = im.span + uniform64(bp->span_base);
   const uint32_t *D = im.dcodes + uniform64(bp->d_base);
   const toc_key *key = im.key + uniform64(bp->code_base);
   const toc_link *link = im.link + (uniform64(bp->deep_base) - (int64_t)t.n1);
+  constexpr int kH = (N + kWave - 1) / kWave;            // 64-column parts of the tile
+  const int parts_k = min(kH, (k - q0 + kWave - 1) / kWave);
   for (int r = wave; r < t.n_rows; r += kThreads / kWave) {
-    for (int h = 0; h < N; h += kWave) {
-      const int q = q0 + h + lane;
-      const float *Wq = W + min(q, k - 1);
-      float sum = 0.0f, part = 0.0f;
-      uint32_t n = 0;
-      for (uint32_t e = span[r]; e < span[r + 1]; ++e) {
-        for (uint32_t c = D[e];;) {
-          const toc_key y = key[c];
-          part = fmaf(y.val, Wq[(int64_t)y.col * ldw], part);
-          if ((++n & 15u) == 0) sum += part, part = 0.0f;
-          if (c < t.n1) break;
-          c = link[c].parent;
+    float sum[kH] = {}, part[kH] = {};
+    uint32_t n = 0;
+    const uint32_t end = span[r + 1];
+    for (uint32_t e = span[r]; e < end; e += kWave) {
+      uint32_t c = e + (uint32_t)lane < end ? D[e + (uint32_t)lane] : kRoot;
+      uint64_t on;
+      while ((on = __ballot(c != kRoot)) != 0) {
+        const toc_key y = c != kRoot ? key[c] : toc_key{0u, 0.0f};
+        c = c != kRoot && c >= t.n1 ? link[c].parent : kRoot;
+        const int col = (int)y.col, val = __float_as_int(y.val);
+        while (on) {
+          float x[8][kH];
+          int v[8];
+          const int count = min((int)__popcll(on), 8);
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            const int l = __builtin_ctzll(on | 1ull << 63);      // (past the last: any lane)
+            if (u < count) on &= on - 1;
+            v[u] = __builtin_amdgcn_readlane(val, l);
+            const float *Wr = W + (int64_t)__builtin_amdgcn_readlane(col, l) * ldw;
+#pragma unroll
+            for (int h = 0; h < kH; ++h)
+              if (h < parts_k) x[u][h] = Wr[min(q0 + h * kWave + lane, k - 1)];
+          }
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            if (u >= count) break;
+            ++n;
+#pragma unroll
+            for (int h = 0; h < kH; ++h) {
+              if (h < parts_k) part[h] = fmaf(__int_as_float(v[u]), x[u][h], part[h]);
+              if ((n & 15u) == 0) sum[h] += part[h], part[h] = 0.0f;
+            }
+          }
         }
       }
-      if (h + lane < N && q < k) Rb[(int64_t)r * ldr + q] = sum + part;
+    }
+#pragma unroll
+    for (int h = 0; h < kH; ++h) {
+      const int q = h * kWave + lane;
+      if (q < N && q0 + q < k) Rb[(int64_t)r * ldr + q0 + q] = sum[h] + part[h];
     }
   }
 }
@@ -1036,7 +1140,6 @@ size_t pass_bytes(const toc_dev *d, int64_t n) {
 }
 // Asked for at most; more is used when given.
 constexpr size_t kPassBytes = TOC_NOALLOC_SCRATCH_BYTES;
-constexpr int64_t kExpandCols = 16384;            // columns whose counts the LDS holds
 constexpr size_t kExpandLds = 152 * 1024;
 
 // Batches full of deep codes (dense quantised ones).
@@ -1128,7 +1231,7 @@ bool mfma_suits(const toc_dev *d, int32_t k, bool right) {
   const toc_dev_info &n = d->info;
   if (k < 2 || d->max_rows > 256 || d->max_ucols < 1) return false;
   // a tile has one cell for a tuple and a column
-  if (!d->columns_rise) return false;
+  if (d->max_tree_pairs < 0) return false;
   if (n.n_cols > kExpandCols || pass_bytes(d, least_batches(d, k, right)) > kPassBytes) return false;
   const int64_t cells = n.n_rows * d->max_ucols;
   if (n.nnz * 16 < cells) return false;

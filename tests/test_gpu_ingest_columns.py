@@ -1,4 +1,5 @@
-"""Physical bytes whose tuples hold a column more than once, or out of order.  The
+"""Physical bytes whose tuples hold a column more than once, or out of order (or values
+that the matrix-core products do not take).  The
 encoders refuse such tuples, but bytes made elsewhere can describe them: every code
 occurs once in a tuple, as the ingest asks, and the bytes are otherwise whole.  The
 products sum all pairs of a tuple (at most 100 terms a sum, each rounded to binary32:
@@ -49,6 +50,14 @@ def _out_of_order():
     return _encoded(rows, 9)
 
 
+def _values_out_of_range():
+    """Whole tuples with a value of 2^-50."""
+    rng = np.random.default_rng(7)
+    rows = [[(j, O.f32_bits(float(rng.integers(1, 4)) * (2.0 ** -50 if i == j else 1))) for j in range(12)]
+            for i in range(30)]
+    return _encoded(rows, 12)
+
+
 def _dense(I, D, cols):
     """Sums of each tuple's values by column, and of their absolute values."""
     rows = O.decode(I, D)
@@ -61,7 +70,7 @@ def _dense(I, D, cols):
 
 
 def test_the_bytes_are_accepted():
-    for make in (_repeated, _columns_of_many_pairs, _out_of_order):
+    for make in (_repeated, _columns_of_many_pairs, _out_of_order, _values_out_of_range):
         I, D, cols = make()
         assert all(len(set(codes)) == len(codes) for codes in D)
         info = T.toc_phys_info_get(np.frombuffer(O.pack_physical(I, D), np.uint8))
@@ -69,7 +78,7 @@ def test_the_bytes_are_accepted():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("make", [_repeated, _columns_of_many_pairs, _out_of_order])
+@pytest.mark.parametrize("make", [_repeated, _columns_of_many_pairs, _out_of_order, _values_out_of_range])
 @pytest.mark.parametrize("k", [1, 2, 20])
 def test_products(make, k):
     I, D, cols = make()

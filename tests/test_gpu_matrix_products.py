@@ -185,7 +185,7 @@ def test_passes_of_a_smaller_workspace(left):
         assert torch.equal(outs[0], out)
 
 
-@pytest.mark.parametrize("bad", [np.inf, np.nan, 1e-30, 1e30, 3e38])
+@pytest.mark.parametrize("bad", [np.inf, np.nan, 1e-41, 1e-38, 1e-30, 1e-25, 1e12, 1e30, 3e38])
 def test_operands_outside_the_split(bad):
     """A non-finite or extreme entry of W or G reaches only what it multiplies."""
     k = 2
@@ -222,22 +222,60 @@ def test_operands_outside_the_split(bad):
             assert not np.isfinite(got[held]).any()
 
 
+@pytest.mark.parametrize("mapped", [False, True])
 @pytest.mark.parametrize("scale", [2.0 ** -40, 2.0 ** 55])
-def test_values_outside_the_split(scale):
+def test_values_outside_the_split(scale, mapped):
+    """An image of such values goes to the general kernels; values that toc_map_values has
+    moved outside are taken term by term."""
     B = _batches([66, 40], 35, 8950, density=0.9, n_values=5, prefix_copy=0.5)
-    B.val = (B.val * np.float32(scale)).astype(np.float32)
+    if not mapped:
+        B.val = (B.val * np.float32(scale)).astype(np.float32)
     dev = _upload(B)
-    k = 3
+    if mapped:
+        T.toc_map_values(dev, T.TOC_MAP_SCALE, scale)
+        B.val = (B.val * np.float32(scale)).astype(np.float32)
     rng = np.random.default_rng(6)
-    W = rng.standard_normal((35, k)).astype(np.float32)
-    G = rng.standard_normal((106, k)).astype(np.float32)
-    R = torch.empty((106, k), device=DEV)
-    out = torch.empty((70, k), device=DEV)
-    ws = _ws(dev, T.TOC_OP_RIGHT, k)
-    T.toc_right_mul(dev, torch.from_numpy(W).to(DEV), R, ws)
-    assert took_matrix_cores(ws, tree_pairs(B), B.n_cols)
-    ws = _ws(dev, T.TOC_OP_LEFT, k)
-    T.toc_left_mul(dev, torch.from_numpy(G).to(DEV), out, False, ws)
-    assert took_matrix_cores(ws, tree_pairs(B), B.n_cols)
-    _check_right(B, R.cpu().numpy(), W)
-    _check_left(B, out.cpu().numpy(), G)
+    for k in (3, 20):
+        W = rng.standard_normal((35, k)).astype(np.float32)
+        G = rng.standard_normal((106, k)).astype(np.float32)
+        R = torch.empty((106, k), device=DEV)
+        out = torch.empty((70, k), device=DEV)
+        for op, call, X, Y in ((T.TOC_OP_RIGHT, T.toc_right_mul, W, R),
+                               (T.TOC_OP_LEFT, lambda d, x, y, w: T.toc_left_mul(d, x, y, False, w), G, out)):
+            ws = _ws(dev, op, k)
+            call(dev, torch.from_numpy(X).to(DEV), Y, ws)
+            if op == T.TOC_OP_LEFT or k == 3:       # (wider right products of so few codes: the general)
+                assert took_matrix_cores(ws, tree_pairs(B), 35) == mapped
+        _check_right(B, R.cpu().numpy(), W)
+        _check_left(B, out.cpu().numpy(), G)
+
+
+def test_small_values_are_not_slow():
+    """Values of G and W far below the others (saturated gradients, decayed weights) take the
+    matrix cores too: within three times the time without them (a tile taken term by term
+    takes twenty times)."""
+    B = _batches([250] * 64, 100, 8990, density=0.9, n_values=400, prefix_copy=0.0)
+    dev, k = _upload(B), 300
+    W, G = torch.randn(100, k, device=DEV), torch.randn(64 * 250, k, device=DEV)
+    R, out = torch.empty_like(G), torch.empty(64 * 100, k, device=DEV)
+    ws = [_ws(dev, op, k) for op in (T.TOC_OP_RIGHT, T.TOC_OP_LEFT)]
+
+    def time(call):
+        best = float("inf")
+        for _ in range(8):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            call()
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    calls = (lambda: T.toc_right_mul(dev, W, R, ws[0]), lambda: T.toc_left_mul(dev, G, out, False, ws[1]))
+    usual = [time(c) for c in calls]
+    for ws_op in ws:
+        assert took_matrix_cores(ws_op, tree_pairs(B), 100)
+    for x in (W, G):
+        x[torch.rand_like(x) < 0.01] = 1e-25
+    for c, t in zip(calls, usual):
+        assert time(c) < 3 * t
