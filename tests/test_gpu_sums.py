@@ -3,9 +3,11 @@ fp32 additions short, so |gpu - oracle| <= 1e-5 * S holds by construction and no
 by luck (Theorems 1 and 2 are exact only in exact arithmetic).
 
 * Many work items per persistent worker on the dense quantised workload (250 x
-  1,000 batches, k = 200): the right product takes the staged kernel (the deep H
+  1,000 batches, k = 200), uploaded with a batch of 257 rows, which the matrix-core
+  kernels do not take: the right product takes the staged kernel (the deep H
   rows of a batch do not fit in LDS) and each worker takes several (batch, column
-  tile) items in turn, reloading its W tile and reusing its workspace slot.
+  tile) items in turn, reloading its W tile and reusing its workspace slot.  Without
+  that batch the same products run on the matrix cores.
 * Adversarial sums: one large term followed by hundreds of terms a quarter of an
   ulp of it.  Summed serially in binary32 every small term is lost and the error
   exceeds 1e-5 * S (checked on the CPU below); summed in blocks it stays far
@@ -19,6 +21,7 @@ import pytest
 
 import oracle as O
 import paper_1702_06943_amd as T
+from matrix_path import took_matrix_cores, tree_pairs
 from workloads import Batches, config_batches, config_G, config_W
 from workloads.parallel import default_workers
 
@@ -37,25 +40,39 @@ def _upload(B, flags=0):
     return dev, buf, T.toc_dev_info_get(dev)
 
 
-def _right(dev, info, W):
+def _call(product, ws, info, path):
+    """Runs it; path: (whether the matrix-core kernels take it, the batches' tree pairs)."""
+    if ws is not None:
+        ws.fill_(float("nan"))
+    product()
+    torch.cuda.synchronize()
+    if path is not None:
+        assert took_matrix_cores(ws, path[1], info["n_cols"]) == path[0]
+
+
+def _tall(n_cols, n_rows=257):
+    """A batch of one entry a row, more rows than the matrix-core kernels take."""
+    i = np.arange(n_rows)
+    return _batch([([j % n_cols], [1.0 + j]) for j in i], n_cols)
+
+
+def _right(dev, info, W, path=None):
     k = W.shape[1]
     Wd = torch.from_numpy(np.ascontiguousarray(W)).to(DEV)
     R = torch.full((info["n_rows"], k), float("nan"), device=DEV)
     ws_n, _ = T.toc_workspace_size(dev, T.TOC_OP_RIGHT, k)
     ws = torch.empty(max(ws_n, 4) // 4, device=DEV) if ws_n else None
-    T.toc_right_mul(dev, Wd, R, ws)
-    torch.cuda.synchronize()
+    _call(lambda: T.toc_right_mul(dev, Wd, R, ws), ws, info, path)
     return R.cpu().numpy().astype(np.float64)
 
 
-def _left(dev, info, G):
+def _left(dev, info, G, path=None):
     k = G.shape[1]
     Gd = torch.from_numpy(np.ascontiguousarray(G)).to(DEV)
     out = torch.full((info["n_batches"] * info["n_cols"], k), float("nan"), device=DEV)
     ws_n, _ = T.toc_workspace_size(dev, T.TOC_OP_LEFT, k)
     ws = torch.empty(max(ws_n, 4) // 4, device=DEV) if ws_n else None
-    T.toc_left_mul(dev, Gd, out, False, ws)
-    torch.cuda.synchronize()
+    _call(lambda: T.toc_left_mul(dev, Gd, out, False, ws), ws, info, path)
     return out.cpu().numpy().astype(np.float64)
 
 
@@ -91,7 +108,8 @@ def test_dense_quantised_many_items_per_worker():
     """96 batches of the dense quantised workload at k = 200: 7 column tiles per
     batch, 84 items on each XCD's 32 workers, so every worker runs several items
     (right: staged kernel, W tile reloaded between items, workspace slot reused;
-    left: tiled kernel with tree rows partly in the workspace).  Every batch is
+    left: tiled kernel with tree rows partly in the workspace) when a batch of 257 rows
+    keeps the products off the matrix cores, which take them without it.  Every batch is
     compared element by element with the oracle; decode bit for bit."""
     import oracle_jobs
     cfg, nb, k = "c4", 96, 200
@@ -99,14 +117,19 @@ def test_dense_quantised_many_items_per_worker():
     W = config_W(cfg, k)
     G = config_G(cfg, 0, nb, k)
     dev, buf, info = _upload(B)
-    R = _right(dev, info, W)
-    out = _left(dev, info, G)
+    pairs = tree_pairs(B)
+    results = [(_right(dev, info, W, (True, pairs)), _left(dev, info, G, (True, pairs)))]
     rp = torch.empty(info["n_rows"] + 1, dtype=torch.int64, device=DEV)
     cc = torch.empty(info["nnz"], dtype=torch.int32, device=DEV)
     vv = torch.empty(info["nnz"], dtype=torch.float32, device=DEV)
     T.toc_decode_csr(dev, rp, cc, vv)
     torch.cuda.synchronize()
     rp, cc, vv = rp.cpu().numpy(), cc.cpu().numpy(), vv.cpu().numpy().view(np.uint32)
+    more = _tall(B.n_cols)
+    pairs = np.concatenate([pairs, tree_pairs(more)])
+    tdev, tbuf, tinfo = _upload(Batches.concat([B, more]))
+    results.append((_right(tdev, tinfo, W, (False, pairs)),
+                    _left(tdev, tinfo, np.concatenate([G, G[:257]]), (False, pairs))))
     print(f"{nb} batches uploaded ({info['n_deep']} deep codes); oracle on a pool", flush=True)
     pool = _pool()
     try:
@@ -117,8 +140,9 @@ def test_dense_quantised_many_items_per_worker():
     m, n = B.n_cols, 250
     worst = 0.0
     for b, (Rr, SR, Or, SO, crp, ccol, cval) in enumerate(refs):
-        worst = max(worst, _check(R[b * n:(b + 1) * n], Rr, SR, f"right, batch {b}"))
-        worst = max(worst, _check(out[b * m:(b + 1) * m], Or, SO, f"left, batch {b}"))
+        for R, out in results:
+            worst = max(worst, _check(R[b * n:(b + 1) * n], Rr, SR, f"right, batch {b}"))
+            worst = max(worst, _check(out[b * m:(b + 1) * m], Or, SO, f"left, batch {b}"))
         p0, p1 = int(rp[b * n]), int(rp[(b + 1) * n])
         assert np.array_equal(rp[b * n:(b + 1) * n + 1] - p0, crp), f"decode rowptr, batch {b}"
         assert np.array_equal(cc[p0:p1], ccol), f"decode col, batch {b}"
@@ -143,10 +167,10 @@ def _long_row(n_cols):
     return np.arange(n_cols, dtype=np.int32), v
 
 
-def _right_case(B, k, rows_of_interest=None):
+def _right_case(B, k, path=None):
     dev, buf, info = _upload(B)
     W = np.ones((B.n_cols, k), np.float32)
-    R = _right(dev, info, W)
+    R = _right(dev, info, W, path)
     worst = 0.0
     for b in range(B.n_batches):
         n, rp, c, v = B.batch(b)
@@ -166,16 +190,18 @@ def test_blocked_right_tiled_long_tuple():
     _right_case(B, 32)
 
 
-def test_blocked_right_staged_long_tuple():
+@pytest.mark.parametrize("matrix", [False, True])
+def test_blocked_right_staged_long_tuple(matrix):
     """The same tuple shape (1,000 codes) through the staged right product: the
     batch is uploaded with a dense quantised batch, whose deep H rows do not fit
-    in LDS, so every batch of the upload takes the staged kernel (k = 40: a full
-    and a partial column tile)."""
+    in LDS, and one of 257 rows, so every batch of the upload takes the staged kernel
+    (k = 40: a full and a partial column tile); and through the matrix-core product,
+    which takes the upload without the latter."""
     c4 = config_batches("c4", 3, 1)
     c, v = _long_row(c4.n_cols)
     _assert_adversarial(v)
-    B = Batches.concat([c4, _batch([(c, v)], c4.n_cols)])
-    _right_case(B, 40)
+    B = Batches.concat([c4, _batch([(c, v)], c4.n_cols)] + ([] if matrix else [_tall(c4.n_cols)]))
+    _right_case(B, 40, (matrix, tree_pairs(B)))
 
 
 def test_blocked_right_wide_long_tuple():

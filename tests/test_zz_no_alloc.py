@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 
 import paper_1702_06943_amd as T
+from matrix_path import took_matrix_cores, tree_pairs
 from workloads import Batches, config_batches, config_G
 
 torch = pytest.importorskip("torch")
@@ -25,7 +26,7 @@ def _upload(B):
     return dev, buf, T.toc_dev_info_get(dev)
 
 
-def _both(dev, info, G, accumulate=False, init=None):
+def _both(dev, info, G, accumulate=False, init=None, matrix=None, pairs=None):
     """(toc_left_mul with its own workspace, toc_left_mul_noalloc called through
     the C ABI) on the same inputs."""
     k = G.shape[1]
@@ -42,22 +43,32 @@ def _both(dev, info, G, accumulate=False, init=None):
             assert st == 0, T.lib().toc_last_error()
         else:
             ws_n, _ = T.toc_workspace_size(dev, T.TOC_OP_LEFT, k)
-            ws = torch.empty(max(ws_n, 4) // 4, device=DEV) if ws_n else None
+            ws = torch.full((max(ws_n, 4) // 4,), float("nan"), device=DEV) if ws_n else None
             T.toc_left_mul(dev, Gd, out, accumulate, ws)
+            if matrix is not None:
+                assert took_matrix_cores(ws, pairs, info["n_cols"]) == matrix
         torch.cuda.synchronize()
         outs.append(out.cpu().numpy())
     return outs
 
 
-def test_noalloc_equals_left_mul_two_calls():
-    # call 1: 48 dense quantised batches at k = 64; the full grid's workspace
-    # (one 3.8 MB slot per worker) is beyond the static buffer, so fewer workers run
+@pytest.mark.parametrize("matrix", [False, True])
+def test_noalloc_equals_left_mul_two_calls(matrix):
+    # call 1: 48 dense quantised batches at k = 64, on the matrix cores; or, with a batch of
+    # 257 rows, which those do not take, through the tiled kernel, whose full grid's
+    # workspace (one 3.8 MB slot per worker) is beyond the static buffer, so fewer workers
+    # run
     B1 = config_batches("c4", 0, 48)
+    G1 = config_G("c4", 0, 48, 64)
+    if not matrix:
+        i = np.arange(257)
+        more = Batches(B1.n_cols, [257], np.arange(258), (i % B1.n_cols).astype(np.int32),
+                       (1.0 + i).astype(np.float32))
+        B1, G1 = Batches.concat([B1, more]), np.concatenate([G1, G1[:257]])
     dev1, buf1, info1 = _upload(B1)
     ws_n, _ = T.toc_workspace_size(dev1, T.TOC_OP_LEFT, 64)
     assert ws_n > T.TOC_NOALLOC_SCRATCH_BYTES
-    G1 = config_G("c4", 0, 48, 64)
-    a, b = _both(dev1, info1, G1)
+    a, b = _both(dev1, info1, G1, matrix=matrix, pairs=tree_pairs(B1))
     assert not np.isnan(a).any()
     assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
     del dev1, buf1
