@@ -258,8 +258,9 @@ __global__ __launch_bounds__(kEpBlock) void enc_pairs_kernel(
 // Phase II: workgroup g runs batches g, g + gridDim.x, ...
 //
 // Bound by the latency of the table probes, which miss the L2 (a megabyte per
-// image-like batch): a tuple takes as many dependent probes as its longest match has
-// pairs, plus one to insert its new nodes, where one lane per batch took one per pair.
+// image-like batch): every kEtBlock entries of a tuple take as many dependent probes as the
+// longest match from one of them has pairs, plus one to insert their new nodes, where one
+// lane per batch took one per pair.
 // 256 image-like batches (39,200 pairs each) took 78 ms that way, 1.5 ms now; a larger
 // workgroup gains nothing (157 entries a tuple), more batches run side by side.
 __global__ __launch_bounds__(kEtBlock) void enc_tuples_kernel(
@@ -308,10 +309,11 @@ __global__ __launch_bounds__(kEtBlock) void enc_tuples_kernel(
         w0 = p1 + tid < n_pairs ? Db[p1 + tid] : 0u;          // the next segment's
         w1 = p1 + tid + kEtBlock < n_pairs ? Db[p1 + tid + kEtBlock] : 0u;
         __syncthreads();
-        // the longest match from entry j; slot: where its key was not found
+        // the longest match from entry j (unless an earlier segment's match covers it); slot:
+        // where its key was not found
         uint32_t n = pairs[tid], l = 1, slot = 0;
         uint64_t key = 0;
-        bool more = valid && j + 1 < pe;
+        bool more = valid && (uint32_t)tid >= skip && j + 1 < pe;
         if (more) {
           key = ((uint64_t)n << 32) | pairs[tid + 1];
           slot = mix64(key) & mask;
