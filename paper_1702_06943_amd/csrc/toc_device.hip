@@ -3280,7 +3280,9 @@ toc_status toc_right_mul(const toc_dev *d, const float *W, int32_t k, int64_t ld
     const int lpr = lanes_per_row(d);
     for (int64_t b0 = 0; b0 < nb; b0 += (1 << 30)) {
       const unsigned g = (unsigned)std::min<int64_t>(nb - b0, 1 << 30);
-      // (few batches: a CU's waves for each)
+      // (a CU's waves for each where there is a CU for each: 1,024 threads hold the batch's
+      // codes in registers up to 12,288, 256 up to 3,072; 256 batches, with 256 threads and
+      // with 1,024: image-like 71 and 33 us, one-hot 22 and 19, census 41 and 36)
       switch (lpr) {
 #define TOC_RK1_BLK(L, BLK)                                                                \
   do {                                                                                     \
@@ -3377,17 +3379,23 @@ toc_status left_mul_impl(const toc_dev *d, const float *G, int32_t k, int64_t ld
   if (k == 1 && k1_fits(d, TOC_OP_LEFT)) {
     const size_t lds = k1_lds(d, TOC_OP_LEFT);
     const bool wide_m = m > 4 * kBlock;      // a pass of 4 columns per thread covers 4 kBlock
-    // Few batches leave most CUs idle with a workgroup each: then a batch's columns are
+    // Up to 128 batches leave CUs idle with a workgroup each: then a batch's columns are
     // dealt to several, which each sum every tree code and the leaves of their own
     // columns.  That pays where most codes are leaves (the tree codes' part is done by
-    // each) and a part still has columns for its threads.
-    // 300 sparse text batches (47,236 columns): 256 -> 161 us with 6 parts (as many
-    // workgroups as the LDS lets run at once; half or twice that many are slower).
-    const int64_t parts = d->max_tree * 8 > d->max_codes
-                              ? 1
-                              : std::max<int64_t>(1, std::min<int64_t>({(1536 + nb - 1) / nb, 8, m / kBlock}));
-    // a CU to itself: all its waves for one batch
-    const bool alone = nb * parts <= 256;
+    // each), a part still has columns for its threads, and every part has a CU to itself
+    // (sparse text of 47,236 columns, 20 batches in 1, 4 and 8 parts: 77, 37 and 30 us; 120
+    // batches in 1, 2 and 3: 87, 58 and 107; 256 image-like batches in 1 and 3: 54 and 216).
+    const bool leaves = d->max_tree * 8 <= d->max_codes;
+    const int64_t parts =
+        leaves ? std::max<int64_t>(1, std::min<int64_t>({256 / nb, 8, m / kBlock})) : 1;
+    // 1,024 threads for a batch where two such workgroups to a CU are all there are (512
+    // batches), and, of batches that are mostly leaves, for more of them where the LDS lets
+    // at most four share a CU, or where there are columns for the threads.  256 threads,
+    // then 1,024: 400 one-hot batches 62 and 39 us, 2,000 89 and 141; 400 image-like
+    // batches (157 KB) 228 and 93, 4,000 1929 and 773; of 60 rows (38 KB) 1,200 73 and 56,
+    // of 50 rows (32 KB) 45 and 51; sparse text of 60 rows, 2,000 columns (12 KB), 1,500 66
+    // and 53.
+    const bool big = nb * parts <= 512 || (leaves && (wide_m || lds * 5 > kLdsMax));
     const uint8_t *bb = (const uint8_t *)d->buf;
     const uint32_t *occ_off = (const uint32_t *)(bb + d->layout.occ_off);
     const uint32_t *tlist = (const uint32_t *)(bb + d->layout.tlist);
@@ -3402,9 +3410,8 @@ toc_status left_mul_impl(const toc_dev *d, const float *G, int32_t k, int64_t ld
                        tlist, cols, tchild, b0, m, d->max_rows, d->max_codes, (int)parts, G, ldg,   \
                        out, ldo, accumulate);                                                   \
   } while (0)
-      if (alone && parts > 1) TOC_LK1(4, 1024, true);
-      else if (alone) TOC_LK1(4, 1024, false);
-      else if (parts > 1) TOC_LK1(8, kBlock, true);
+      if (parts > 1) TOC_LK1(4, 1024, true);
+      else if (big) TOC_LK1(4, 1024, false);
       else if (wide_m) TOC_LK1(8, kBlock, false);
       else TOC_LK1(4, kBlock, false);
 #undef TOC_LK1
