@@ -718,7 +718,7 @@ def measured_copy_bandwidth(stream, mib=4096, reps=5):
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("toc_device.hip", "toc_host.cpp", "toc_internal.h"):
+    for f in ("toc_device.hip", "toc_mfma.hip", "toc_host.cpp", "toc_internal.h"):
         h.update(open(os.path.join(HERE, "paper_1702_06943_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

@@ -209,3 +209,18 @@ def test_encode_device_host_checks():
     assert lib.toc_encode_device(*bad) == T.TOC_EINVAL
     assert lib.toc_encode_device(0, None, 5, None, None, None, 0, 0, None, None, None, None,
                                  None, None, None, 0, None) == 0
+
+
+def test_bench_traffic_is_of_the_current_kernels(monkeypatch):
+    """The measured HBM bytes that bench.py reports are dropped when a source of the products'
+    kernels has changed: its hash reads them all."""
+    import bench
+    read = []
+
+    def opened(path, *args):
+        read.append(path.rsplit("/", 1)[-1])
+        return open(path, *args)
+
+    monkeypatch.setattr(bench, "open", opened, raising=False)
+    bench.kernel_source_hash()
+    assert {"toc_device.hip", "toc_mfma.hip", "toc_host.cpp", "toc_internal.h"} <= set(read)
