@@ -227,9 +227,9 @@ toc_status toc_dev_layout_get(const toc_dev *dev, toc_layout *layout);
 /* ---------------------------------------------------------------------------
  * Device operations.  Workspace: toc_workspace_size gives the bytes an op needs
  * to run in one pass over all batches; an op given less (but at least its
- * per-batch minimum, returned in *min_bytes when not NULL) runs in several
- * passes or with other kernels (the same result within rounding); less than the
- * minimum is TOC_ESIZE.  A size of 0 means ws may be NULL.
+ * per-batch minimum, returned in *min_bytes when not NULL), or not 16-byte aligned, runs
+ * in several passes or with other kernels (the same result within rounding); less than
+ * the minimum is TOC_ESIZE.  A size of 0 means ws may be NULL.
  * The workspace is scratch: its contents on entry do not matter.
  * op: TOC_OP_RIGHT, TOC_OP_LEFT, TOC_OP_DECODE.
  * ------------------------------------------------------------------------- */
@@ -265,10 +265,10 @@ toc_status toc_left_mul(const toc_dev *dev, const float *G, int32_t k, int64_t l
 /* Left multiplication without any allocation, for callers that cannot allocate
  * device memory (work captured into a HIP graph, tight serving loops, harnesses
  * that forbid hipMalloc).  The same product as toc_left_mul given the workspace that
- * toc_workspace_size asks for, bit for bit, with no workspace argument: the workspace
- * is a static device buffer of TOC_NOALLOC_SCRATCH_BYTES that the library holds on
- * every GPU it runs on until the process ends (its address is looked up on the first
- * call on each device).
+ * toc_workspace_size asks for, 16-byte aligned, bit for bit, with no workspace argument:
+ * the workspace is a static device buffer of TOC_NOALLOC_SCRATCH_BYTES that the library
+ * holds on every GPU it runs on until the process ends (its address is looked up on the
+ * first call on each device).
  * When the full grid's per-worker slots do not fit in it, fewer persistent
  * workers run (slower, same result).  Calls on one GPU share that buffer: calls
  * that overlap in time on one GPU (other streams, other host threads) race and

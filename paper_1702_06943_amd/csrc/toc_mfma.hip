@@ -554,12 +554,14 @@ struct Feed {
 // groups, a column each, so that one barrier per chunk is enough) from entry words
 // that were loaded a chunk ahead.  So G is read once per batch and A once per 128
 // columns of G, by workgroups of one XCD that run at the same time and share it in
-// the L2.  250-row batches, vector kernel then this one: 400 image-like batches at
-// k = 300 415 -> 300 us (655 MB, 2.2 TB/s), 100 dense quantised ones at k = 200 1374 ->
-// 281 us, of which 97 the expansion.  What is left is the serial part of a chunk: two
-// waves per SIMD, whose fill (LDS writes of single values) and matrix work overlap
-// little.  One wave of a SIMD filling while the other multiplies, half a chunk apart,
-// measured 347 against 338 us; bringing the next chunk's lines into the L2 first 401.
+// the L2.  250-row batches, vector kernel then this one with the expansion: 400 image-like
+// batches at k = 300 417 -> 294 us (639 MB, 2.2 TB/s), 100 dense quantised ones at k = 200
+// 1393 -> 264 us, of which 59 the expansion.  What is left is the serial part of a chunk:
+// two waves per SIMD, whose fill (LDS writes of single values) and matrix work overlap
+// little (matrix cores 18 and 22 % busy, LDS 27 and 42 %, more than half of it bank
+// conflicts).  In an earlier form of this kernel, which took 338 us, one wave of a SIMD
+// filling while the other multiplies, half a chunk apart, took 347 us, and bringing the
+// next chunk's lines into the L2 first 401.
 // Tile: [tuples / 8][32 columns] slots of 8 tuples (16 bytes), 36 slots to a row: a
 // matrix operand is one 16-byte read per lane, and a wave's writes (four columns, 32
 // tuples each) fall into different banks.
@@ -850,8 +852,9 @@ __global__ __launch_bounds__(kThreads, KS == 2 ? 4 : 2) void left_mfma_kernel(
 // part of R in registers (a wave: 64 tuples x 16 NF columns); the used columns of A
 // and the rows of W they name stream through LDS, 32 at a time, double-buffered as
 // in the left product.  W is split into its parts on the way (it stays in the L2).
-// 400 image-like batches at k = 300 381 -> 255 us, 100 dense quantised ones at k = 200
-// 1275 -> 262 us.  NF = 5 (two tiles instead of three at k = 300) spills: 434 us.
+// 400 image-like batches at k = 300 382 -> 262 us, 100 dense quantised ones at k = 200
+// 1278 -> 247 us (matrix cores 22 and 24 % busy).  NF = 5 (two tiles instead of three at
+// k = 300) spills: 434 us.
 // Tiles: A [8][64 WM tuples] slots of 4 columns (8 bytes), W [4][N] slots of 8 rows; a
 // wave owns the 4 columns of one slot row, which it clears and fills by itself.
 // ---------------------------------------------------------------------------
@@ -1214,18 +1217,20 @@ toc_status run(const char *name, K kernel, size_t lds, const toc_dev *d, int n_t
 namespace toc {
 
 // Where these kernels are the faster ones.  Against the vector kernels of
-// toc_device.hip (right / left, us, vector then matrix; 250-row batches):
+// toc_device.hip (right / left, us a call alone, vector then matrix; 250-row batches):
 //  - dense quantised batches, whose many deep codes cost those a table row each:
-//    always (100 batches, k = 200: 1277 -> 266, 1404 -> 291; one batch, k = 8: 317 -> 132,
-//    469 -> 188).  A right product of batches with far fewer codes than nonzeros
-//    runs on the codes instead (400 census batches, k = 20: 122 against 265);
+//    always (100 batches, k = 200: 1305 -> 259, 1416 -> 287; one batch, k = 8: 311 -> 138,
+//    414 -> 210).  A right product of batches with far fewer codes than nonzeros
+//    runs on the codes instead (400 census batches, k = 20: 132 both ways, 50 of 100 rows,
+//    k = 10: 41 against 78; their left products 370 -> 154 and 116 -> 82);
 //  - others (image-like, one-hot): when the pairs of batches and 64-column tiles fill
 //    the chip and more than one tile shares a batch's expansion (400 image-like
-//    batches, k = 300: 400 -> 244, 440 -> 302; 64 batches: 106 -> 60, 115 -> 66; but 64
-//    batches at k = 128: 56 and 61 against 56 and 64, 400 batches of 100 rows at k = 20:
-//    35 and 61 against 63 and 81);
+//    batches, k = 300: 445 -> 278, 494 -> 320; 64 batches: 114 -> 73, 124 -> 75; 150, k =
+//    100: 113 -> 73, 123 -> 76; one-hot batches, left: 400, k = 100 406 -> 186, k = 300
+//    814 -> 394, 150, k = 130 198 -> 160; but 64 image-like batches at k = 128: 66 and 69
+//    against 68 and 73, 400 of 100 rows at k = 20: 44 and 72 against 74 and 89);
 //  - right products of 2 and 3 columns, which only the general kernel took (400
-//    image-like batches, k = 2: 2368 -> 80).
+//    image-like batches, k = 2: 2382 -> 87).
 // Below a sixteenth of the tiles' cells filled (sparse text) the expansion is mostly zeros.
 bool mfma_suits(const toc_dev *d, int32_t k, bool right) {
   const toc_dev_info &n = d->info;

@@ -4,7 +4,7 @@ tree codes need several levels, and with operands that send them term by term.
 
 Bound: |gpu - oracle| <= 1e-5 * S per element, S the sum of the absolute terms: the
 parts' dropped products and the sums' roundings stay below it for any of these
-sizes (at most 256 terms beside the 2^-22 of a product).
+sizes (at most 256 terms, each less 2^-31 of itself at most).
 """
 
 import numpy as np
