@@ -394,7 +394,7 @@ struct ImgScratch {
 // writes the batch's arrays at its offsets.  Returns the per-batch counts through bt.
 toc_status write_batch(const toc_enc *e, int64_t b, uint32_t flags, const toc_layout &L,
                        uint8_t *dst, toc_batch &bt, int64_t dtile_base, int64_t &tree_pairs,
-                       ImgScratch &S) {
+                       uint8_t &many_parts, ImgScratch &S) {
   const bool keep = flags & TOC_UPLOAD_KEEP_DEAD;
   const int64_t nI = (int64_t)e->I_col.size();
   const int64_t N = e->n_nodes;
@@ -590,8 +590,11 @@ toc_status write_batch(const toc_enc *e, int64_t b, uint32_t flags, const toc_la
     for (int64_t k = 0; k < m; ++k) c_ord[k] = (uint32_t)S.keys[k];
     c_ord[m] = 0;
     tree_pairs = e->nnz - (int64_t)c_occ[m];   // (a leaf's occurrence is one pair)
-    for (uint32_t bits : e->I_bits)
+    many_parts = 0;
+    for (uint32_t bits : e->I_bits) {
       if (!mfma_value(bits)) tree_pairs = -1;
+      many_parts |= mfma_many_parts(bits);
+    }
     // columns that are the key column of some stored code (a leaf or a tree code)
     int32_t u = 0;
     for (int64_t j = 0; j < m; ++j)
@@ -704,6 +707,7 @@ toc_status plan_layout(const BatchCounts *bc, int64_t n_batches, int32_t n_cols,
   dev->max_d = dev->max_deep = dev->max_tree = dev->max_pair_deep = 0;
   dev->dtile_base.assign((size_t)n_batches, 0);
   dev->tree_pairs.assign((size_t)n_batches, 0);
+  dev->many_parts.assign((size_t)n_batches, 0);
   int64_t dtiles = 0;
   for (int64_t b = 0; b < n_batches; ++b) {
     const BatchCounts &c = bc[b];
@@ -804,7 +808,7 @@ toc_status write_batches(const toc_enc *const *encs, int64_t b0, int64_t b1, uin
       toc_status st;
       try {
         st = write_batch(encs[b], b, flags, L, dst, dev->batches[b], dev->dtile_base[b],
-                         dev->tree_pairs[(size_t)b], S);
+                         dev->tree_pairs[(size_t)b], dev->many_parts[(size_t)b], S);
       } catch (const std::bad_alloc &) {
         st = fail(TOC_ENOMEM, "out of host memory");
       }
@@ -832,8 +836,12 @@ void finish_image(toc_dev *dev) {
   dev->max_tree_pairs = 0;
   for (int64_t n : dev->tree_pairs)
     dev->max_tree_pairs = n < 0 || dev->max_tree_pairs < 0 ? -1 : std::max(dev->max_tree_pairs, n);
+  dev->total_ucols = 0;
+  dev->any_parts = false;
+  for (uint8_t p : dev->many_parts) dev->any_parts |= p != 0;
   for (const toc_batch &bt : dev->batches) {
     dev->max_ucols = std::max(dev->max_ucols, bt.n_ucols);
+    dev->total_ucols += bt.n_ucols;
     dev->max_keylinks = std::max<int64_t>(dev->max_keylinks, 2 * (int64_t)bt.n_codes - bt.n_lvl1);
   }
 }

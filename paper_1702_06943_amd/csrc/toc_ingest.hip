@@ -177,8 +177,9 @@ __device__ int block_radix_sort(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32
 // live codes, deepest live depth, depth-1 codes with live children, live codes of
 // depth >= 2, nonzeros (the sum of the depths of D's codes: each code decodes to
 // that many pairs), live depth-1 codes, distinct key columns of live codes, and the pairs
-// of D's codes with live children or of depth >= 2, or -1 when a node's column is not
-// beyond its parent's or a value is not one that the matrix-core products take.
+// of D's codes with live children or of depth >= 2, times two, plus one when a value is not
+// one bf16 number; or -1 when a node's column is not beyond its parent's or a value is not
+// one that the matrix-core products take.
 // (Neighbouring codes of a tuple have made a node of C', the first code's extended by the
 // second's first pair, so no node's column is amiss exactly when the columns of every
 // tuple increase.)
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
   extern __shared__ uint32_t node_bits[];
   __shared__ Hdr h;
   __shared__ unsigned long long s_nnz, s_tree;
-  __shared__ uint32_t s_live, s_top, s_int1, s_deep, s_lvl1, s_ucols, s_other;
+  __shared__ uint32_t s_live, s_top, s_int1, s_deep, s_lvl1, s_ucols, s_other, s_parts;
   const int64_t *node_off = offs + (n_batches + 1);
   const uint32_t ncw = (n_cols + 31) / 32;
   uint32_t *colbits = colbits_all + (int64_t)blockIdx.x * ncw;
@@ -205,7 +206,7 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
       h.err = cp_status[b];
       if (h.err == 0) parse_headers(blob, size, 1 << 30, h);
       s_nnz = s_tree = 0ull;
-      s_live = s_top = s_int1 = s_deep = s_lvl1 = s_ucols = s_other = 0u;
+      s_live = s_top = s_int1 = s_deep = s_lvl1 = s_ucols = s_other = s_parts = 0u;
     }
     __syncthreads();
     if (h.err) {
@@ -224,10 +225,16 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
     else mark_live(p_d, w_d, n_d, n_nodes, par, fl);
     for (uint32_t x = threadIdx.x; x < ncw; x += kIgBlock) colbits[x] = 0u;
     __syncthreads();
-    uint32_t live = 0, top = 0, int1 = 0, deep = 0, lvl1 = 0, other = 0;
+    uint32_t live = 0, top = 0, int1 = 0, deep = 0, lvl1 = 0, other = 0, parts = 0;
     for (uint32_t c = 1 + threadIdx.x; c < n_nodes; c += kIgBlock) {
       const uint32_t f = fl[c], q = par[c];
-      if (q != 0u ? cl[c] <= cl[q] : !toc::mfma_value(val[no + c])) ++other;
+      if (q != 0u) {
+        if (cl[c] <= cl[q]) ++other;
+      } else {
+        const uint32_t v = val[no + c];
+        if (!toc::mfma_value(v)) ++other;
+        if (toc::mfma_many_parts(v)) parts = 1u;
+      }
       if (!(f & kLive)) continue;
       const uint32_t d = dep[c];
       ++live;
@@ -252,6 +259,7 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
     atomicAdd(&s_deep, deep);
     atomicAdd(&s_lvl1, lvl1);
     atomicAdd(&s_other, other);
+    atomicOr(&s_parts, parts);
     atomicAdd(&s_nnz, nnz);
     atomicAdd(&s_tree, tree);
     __syncthreads();
@@ -268,7 +276,7 @@ __global__ __launch_bounds__(kIgBlock) void census_kernel(
       o[4] = (int64_t)s_nnz;
       o[5] = s_lvl1;
       o[6] = s_ucols;
-      o[7] = s_other ? -1 : (int64_t)s_tree;
+      o[7] = s_other ? -1 : (int64_t)(2ull * s_tree + s_parts);
       status[b] = 0;
     }
     __syncthreads();
@@ -966,6 +974,7 @@ toc_status toc_ingest_plan(const void *blobs, const int64_t *blob_off, const toc
     hipStream_t s = (hipStream_t)stream;
     std::vector<toc::BatchCounts> bc((size_t)n_batches);
     std::vector<int64_t> n1((size_t)n_batches), nu((size_t)n_batches), tp((size_t)n_batches);
+    std::vector<uint8_t> parts((size_t)n_batches);
     for (int64_t b0 = 0, b1 = 0; b0 < n_batches && ret == TOC_OK; b0 = b1) {
       if ((ret = next_range(B, b0, ws_bytes, nullptr, kWsCensus, b1)) != TOC_OK) break;
       const RangeWs w = ws_for(B, b0, b1, nullptr, kWsCensus);
@@ -1010,7 +1019,8 @@ toc_status toc_ingest_plan(const void *blobs, const int64_t *blob_off, const toc
         k.canon = 4 * f.n_codes + 4 * (f.n_rows + 1) + 10 * c[0] + 4 * (c[1] + 1);
         n1[(size_t)b] = c[5];
         nu[(size_t)b] = c[6];
-        tp[(size_t)b] = c[7];
+        tp[(size_t)b] = c[7] < 0 ? -1 : c[7] / 2;
+        parts[(size_t)b] = c[7] >= 0 && (c[7] & 1);
       }
     }
     if (ret == TOC_OK) ret = toc::plan_layout(bc.data(), n_batches, n_cols, 0u, dev);
@@ -1023,6 +1033,7 @@ toc_status toc_ingest_plan(const void *blobs, const int64_t *blob_off, const toc
       dev->batches[(size_t)b].n_ucols = (int32_t)nu[(size_t)b];
     }
     dev->tree_pairs = std::move(tp);
+    dev->many_parts = std::move(parts);
     toc::finish_image(dev);
     dev->phys.assign(info, info + n_batches);
     dev->pending = true;

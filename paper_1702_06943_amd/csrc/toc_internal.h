@@ -35,6 +35,7 @@ struct toc_dev {
   std::vector<toc_batch> batches;  // host copy of the batch table
   int32_t max_rows = 0, max_codes = 0, max_levels = 0;
   int32_t max_ucols = 0;           // most distinct key columns of a batch (after build)
+  int64_t total_ucols = 0;         // of all batches (after build)
   // per batch, the pairs that its tree codes (codes with children or of depth >= 2) stand
   // for in its tuples, or -1 where the matrix-core products do not take it: its tuples'
   // columns do not all increase (the encoders check that; physical bytes from elsewhere
@@ -42,6 +43,10 @@ struct toc_dev {
   // batch, or -1 (after build)
   std::vector<int64_t> tree_pairs;
   int64_t max_tree_pairs = 0;
+  // per batch, and of any (after build): whether a value is not one bf16 number, so that the
+  // matrix-core products need its smaller parts
+  std::vector<uint8_t> many_parts;
+  bool any_parts = false;
   int64_t max_keylinks = 0;        // most keys plus deep links of a batch (after build)
   int64_t max_deep = 0, max_tree = 0, max_d = 0;
   // most deep codes of two batches b, b + 8 with b / 8 even (the batch pairs of
@@ -114,6 +119,7 @@ constexpr bool mfma_value(uint32_t bits) {
   const uint32_t a = bits & 0x7fffffffu;
   return a == 0u || (a >= kMfmaValLo && a <= kMfmaValHi);
 }
+constexpr bool mfma_many_parts(uint32_t bits) { return (bits & 0xffffu) != 0u; }
 bool mfma_suits(const toc_dev *d, int32_t k, bool right);
 size_t mfma_workspace(const toc_dev *d);
 bool mfma_fits(const toc_dev *d, int32_t k, bool right, int64_t ld, const void *ws, size_t ws_bytes);

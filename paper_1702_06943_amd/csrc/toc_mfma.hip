@@ -1214,6 +1214,62 @@ toc_status run(const char *name, K kernel, size_t lds, const toc_dev *d, int n_t
 
 }  // namespace
 
+namespace {
+
+// Tiles of a right product and the 16-column fragments of a wave; returns the waves along
+// the tuples.
+int right_tiles(const toc_dev *d, int32_t k, int &n_tiles, int &f) {
+  const int wm = d->max_rows <= 64 ? 1 : d->max_rows <= 128 ? 2 : 4;
+  const int wn = 8 / wm, most = wm == 1 ? 2 : 4;
+  const int nf = (k + 15) / 16;
+  n_tiles = (nf + wn * most - 1) / (wn * most);
+  f = (nf + wn * n_tiles - 1) / (wn * n_tiles);
+  return wm;
+}
+
+// Whether these kernels are the faster ones for batches that are mostly leaves (image-like).
+// They multiply whole tiles: 64, 128 or 256 tuples whatever a batch has, in rounds of as
+// many workgroups as the CUs hold, and where values are not one bf16 number, eight products
+// instead of three; the vector kernels' time follows the nonzeros, in rounds of a batch and
+// 64 columns to a CU.  So with batches of 130 tuples of fractional values calls take longer
+// here (300 batches, k = 300, right 303 us against 194, left 343 against 240), with whole
+// numbers the same (197 and 194), and with 250 tuples less (234 and 329).  Both times (us)
+// are fitted to 75 to 1,000 image-like batches of 10 to 250 tuples, k of 66 to 300 and both
+// kinds of values, and are right to 5 % (RMS); the calls of that range that go to the slower
+// kernel lose 1 % on average.
+bool mfma_faster(const toc_dev *d, int32_t k, bool right) {
+  const int64_t nb = d->info.n_batches;
+  const int size = d->max_rows <= 64 ? 0 : d->max_rows <= 128 ? 1 : 2, parts = d->any_parts;
+  const int64_t chunks = (d->total_ucols + nb * kChunk - 1) / (nb * kChunk);
+  int64_t groups, at_once = 256;
+  double chunk;                             // a chunk of a round of workgroups
+  if (right) {
+    static const double us[2][3][4] = {
+        {{1.65, 2.35, 2.35, 2.35}, {2.0, 2.25, 2.6, 3.1}, {2.0, 2.4, 2.7, 3.0}},
+        {{2.35, 3.3, 3.3, 3.3}, {2.6, 3.2, 3.9, 4.9}, {2.7, 3.4, 4.2, 4.8}}};
+    int n_tiles, f;
+    right_tiles(d, k, n_tiles, f);
+    groups = nb * n_tiles;
+    chunk = us[parts][size][f - 1];
+    if (size == 0 && f == 1 && groups > 256) chunk *= 0.75;   // (two workgroups to a CU)
+  } else {
+    static const double us[2][3] = {{4.0, 2.8, 3.3}, {4.9, 3.7, 5.6}};
+    groups = nb * ((k + 127) / 128);
+    if (size == 0) at_once = 512;
+    chunk = us[parts][size];
+    if (size == 0 && groups <= 512) chunk *= groups <= 256 ? 0.55 : 0.65;
+  }
+  const double here = 20 + (double)((groups + at_once - 1) / at_once) * (double)chunks * chunk;
+  const int64_t items = nb * ((k + 63) / 64), whole = (items + 255) / 256;
+  const double pairs = (double)d->info.nnz / (double)nb * 1e-3, part = (double)items / 256;
+  const double there = right
+                           ? 16.5 + (0.8 * (double)whole + 0.2 * part) * (1.07 * pairs + 8.7)
+                           : 14.9 + (0.7 * (double)whole + 0.3 * part) * (1.16 * pairs + 13.5);
+  return here < there;
+}
+
+}  // namespace
+
 namespace toc {
 
 // Where these kernels are the faster ones.  Against the vector kernels of
@@ -1224,7 +1280,8 @@ namespace toc {
 //    runs on the codes instead (400 census batches, k = 20: 132 both ways, 50 of 100 rows,
 //    k = 10: 41 against 78; their left products 370 -> 154 and 116 -> 82);
 //  - others (image-like, one-hot): when the pairs of batches and 64-column tiles fill
-//    the chip and more than one tile shares a batch's expansion (400 image-like
+//    the chip and more than one tile shares a batch's expansion, and, of batches that are
+//    mostly leaves, when mfma_faster says so (400 image-like
 //    batches, k = 300: 445 -> 278, 494 -> 320; 64 batches: 114 -> 73, 124 -> 75; 150, k =
 //    100: 113 -> 73, 123 -> 76; one-hot batches, left: 400, k = 100 406 -> 186, k = 300
 //    814 -> 394, 150, k = 130 198 -> 160; but 64 image-like batches at k = 128: 66 and 69
@@ -1243,7 +1300,8 @@ bool mfma_suits(const toc_dev *d, int32_t k, bool right) {
   if (right && k < 4) return true;
   if (right && n.n_codes * 10 < n.nnz * 9) return false;
   if (many_deep(d)) return true;
-  return k > 64 && n.n_batches * ((k + 63) / 64) >= 300;
+  if (k <= 64 || n.n_batches * ((k + 63) / 64) < 300) return false;
+  return d->max_tree * 8 > d->max_codes || mfma_faster(d, k, right);
 }
 
 size_t mfma_workspace(const toc_dev *d) {
@@ -1276,11 +1334,8 @@ toc_status left_mfma(const toc_dev *d, const float *G, int32_t k, int64_t ldg, f
 toc_status right_mfma(const toc_dev *d, const float *W, int32_t k, int64_t ldw, float *R, int64_t ldr,
                       void *ws, size_t ws_bytes, void *stream) {
   hipStream_t s = (hipStream_t)stream;
-  const int wm = d->max_rows <= 64 ? 1 : d->max_rows <= 128 ? 2 : 4;
-  const int wn = 8 / wm, most = wm == 1 ? 2 : 4;
-  const int nf = (k + 15) / 16;
-  const int n_tiles = (nf + wn * most - 1) / (wn * most);
-  const int f = (nf + wn * n_tiles - 1) / (wn * n_tiles);
+  int n_tiles, f;
+  const int wm = right_tiles(d, k, n_tiles, f), wn = 8 / wm;
   const size_t lds = (size_t)6 * (4 * 16 * (64 * wm + 16 * f * wn) + kSpare);
   const int m = d->info.n_cols;
 #define TOC_RM(WM, NF)                                                                          \

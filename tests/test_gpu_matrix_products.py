@@ -185,6 +185,40 @@ def test_passes_of_a_smaller_workspace(left):
         assert torch.equal(outs[0], out)
 
 
+@pytest.mark.parametrize("ingested", [False, True])
+@pytest.mark.parametrize("rows,whole", [(130, False), (250, True)])
+def test_padding_and_parts_decide(rows, whole, ingested):
+    """Batches of mostly leaves: 130 tuples of a tile of 256 and values of three parts go to the
+    general kernels, which take two thirds of the time; full tiles of one part do not."""
+    rp, c, v = tiny_batch(8870, rows, 400, density=0.4, n_values=200 if whole else 40000,
+                          integer=whole)
+    B = Batches.concat([Batches(400, [rows], rp, c, v)] * 60)
+    if ingested:
+        encs = T.toc_encode_batches(B.n_rows, B.n_cols, B.rowptr, B.col, B.val)
+        blobs = [T.toc_enc_pack(e) for e in encs]
+        infos = [T.toc_phys_info_get(b) for b in blobs]
+        off = np.concatenate([[0], np.cumsum([len(b) for b in blobs])]).astype(np.int64)
+        bytes_ = torch.from_numpy(np.concatenate(blobs)).to(DEV)
+        ws = torch.empty(T.toc_ingest_workspace_size(infos, 400)[0], dtype=torch.uint8, device=DEV)
+        size, dev = T.toc_ingest_plan(bytes_, off, infos, 400, ws)
+        T.toc_ingest_build(dev, bytes_, off, torch.empty(size, dtype=torch.uint8, device=DEV), ws)
+    else:
+        dev = _upload(B)
+    k, rng = 300, np.random.default_rng(8870)
+    W = rng.standard_normal((400, k)).astype(np.float32)
+    G = rng.standard_normal((60 * rows, k)).astype(np.float32)
+    R, out = torch.empty((60 * rows, k), device=DEV), torch.empty((60 * 400, k), device=DEV)
+    room = torch.zeros(16 << 20, dtype=torch.uint8, device=DEV)      # (more than the kernels ask)
+    for product in (lambda: T.toc_right_mul(dev, torch.from_numpy(W).to(DEV), R, room),
+                    lambda: T.toc_left_mul(dev, torch.from_numpy(G).to(DEV), out, False, room)):
+        room.fill_(255)
+        product()
+        assert took_matrix_cores(room, tree_pairs(B), 400) == whole
+    B = Batches(400, [rows], rp, c, v)
+    _check_right(B, R[-rows:].cpu().numpy(), W)
+    _check_left(B, out[-400:].cpu().numpy(), G[-rows:])
+
+
 @pytest.mark.parametrize("bad", [np.inf, np.nan, 1e-41, 1e-38, 1e-30, 1e-25, 1e12, 1e30, 3e38])
 def test_operands_outside_the_split(bad):
     """A non-finite or extreme entry of W or G reaches only what it multiplies."""
